@@ -9,6 +9,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <type_traits>
 
 // Everything here is also host-callable, so that host-side checks can run the
 // same arithmetic.
@@ -431,11 +432,16 @@ template <class FT> FDK_HD void mom_full(const Prim<FT>& s, Mom<FT>& m) {
   m.mu[1] = s.U;
   mu_rec(m.mu, s.U, s.i2l);
 }
-// half line: sgn = +1 (u > 0) or -1 (u < 0)
+// half line: sgn = +1 (u > 0) or -1 (u < 0); <1> and <u> - U <1>
+template <class FT> FDK_HD void half_moms(const Prim<FT>& s, FT sgn, FT& m0, FT& x) {
+  FT sl = m_sqrt(s.lam);
+  m0 = FT(0.5) * m_erfc(-sgn * sl * s.U);
+  // 1/(2 sqrt(pi lambda)) = (1/(2 lambda)) sqrt(lambda) / sqrt(pi): no second square root
+  x = sgn * m_exp(-s.lam * s.U * s.U) * (s.i2l * sl) * FT(0.56418958354775628695);
+}
 template <class FT> FDK_HD void mom_half(const Prim<FT>& s, FT sgn, Mom<FT>& m) {
   FT sl = m_sqrt(s.lam);
   m.mu[0] = FT(0.5) * m_erfc(-sgn * sl * s.U);
-  // 1/(2 sqrt(pi lambda)) = (1/(2 lambda)) sqrt(lambda) / sqrt(pi): no second square root
   m.mu[1] = s.U * m.mu[0] + sgn * m_exp(-s.lam * s.U * s.U) * (s.i2l * sl) * FT(0.56418958354775628695);
   mu_rec(m.mu, s.U, s.i2l);
 }
@@ -476,6 +482,28 @@ template <class FT> FDK_HD TimeCoef<FT> time_coef(FT dt, FT tau) {
   // tau = 0 (p_l = p_r without a c1 term): the tau -> 0+ limit, exp(-T/tau) = 0
   FT Eh = val(tau) > 0 ? m_exp(-FT(0.5) * dt / tau) : FT(0);
   FT Ef = Eh * Eh;
+  r.e1 = Ef;
+  FT idt = FT(1) / dt;
+  if constexpr (std::is_same_v<FT, double>) {
+    // The fit written out: with s = tau / dt, E = exp(-dt / (2 tau)) and
+    // o = 1 - E the ten combinations (4 q(dt/2) - q(dt)) / dt and
+    // 4 (q(dt) - 2 q(dt/2)) / dt^2 of the integrals reduce to four numbers.
+    const FT s = tau * idt, o = FT(1) - Eh;
+    const FT c3 = s * o * (FT(2) + o);
+    const FT c4 = tau * ((FT(2) * Eh - Ef) - FT(2) * c3);
+    const FT t0 = FT(4) * s * (o * o), t1 = FT(4) * s * (o * (Eh - FT(2) * s * o));
+    r.c[0] = FT(1) - c3;
+    r.c[1] = -tau - c4;
+    r.c[2] = -tau * r.c[0];
+    r.c[3] = c3;
+    r.c[4] = c4;
+    r.ct[0] = t0 * idt;
+    r.ct[1] = t1;
+    r.ct[2] = FT(1) - s * t0;
+    r.ct[3] = -r.ct[0];
+    r.ct[4] = -t1;
+    return r;
+  }
   FT Th = FT(0.5) * dt, Tf = dt;
   FT qh[5], qf[5];
   qh[0] = Th - tau * (FT(1) - Eh);
@@ -488,14 +516,12 @@ template <class FT> FDK_HD TimeCoef<FT> time_coef(FT dt, FT tau) {
   qf[3] = tau * (FT(1) - Ef);
   qh[4] = tau * ((Th + FT(2) * tau) * Eh - FT(2) * tau);
   qf[4] = tau * ((Tf + FT(2) * tau) * Ef - FT(2) * tau);
-  FT idt = FT(1) / dt;
   FT idt2 = FT(4) * idt * idt;
 #pragma unroll
   for (int k = 0; k < 5; ++k) {
     r.c[k] = (FT(4) * qh[k] - qf[k]) * idt;
     r.ct[k] = (qf[k] - FT(2) * qh[k]) * idt2;
   }
-  r.e1 = Ef;
   return r;
 }
 
@@ -586,8 +612,11 @@ FDK_HD void side_terms(const Prim<FT>& s, const Mom<FT>& h, const FT* n, const F
   }
 }
 
+// The solver from moment vectors of psi, as App. A writes it.  The FP32-flux
+// variant runs it (its results stay those of this arithmetic); FP64 runs the
+// form in primitive slopes below.
 template <class FT, int DIM, bool VALUES>
-FDK_HD void gks_iface(const Consts& k, FT dt, GksIO<FT, DIM>& io) {
+FDK_HD void gks_iface_moments(const Consts& k, FT dt, GksIO<FT, DIM>& io) {
   constexpr int N = DIM + 2;
   const FT K = FT(k.K), gam = FT(k.gamma), iKd = FT(k.inv_Kd);
   const bool both = VALUES || k.mu > 0;  // F and We are needed for the values or the Prandtl fix
@@ -681,12 +710,281 @@ FDK_HD void gks_iface(const Consts& k, FT dt, GksIO<FT, DIM>& io) {
   }
 }
 
+// ------------------------------------- the solver in primitive slopes
+// A slope a.psi of a Maxwellian is the derivative of its logarithm.  With the
+// derivatives of (rho, U, V, theta), theta = p / rho = 1 / (2 lambda), and the
+// peculiar velocities c = u - U, v' = v - V:
+//   a.psi = r + (c U_x + v' V_x) / theta + ((c^2 + v'^2 + xi^2) / theta - (K + dim)) theta_x / (2 theta),
+// r = rho_x / rho.  Everything but u is integrated over full lines, where
+// the moments of v' and xi are closed: the weights 1, v' and
+// e' = (v'^2 + xi^2) / 2 leave polynomials of u,
+//   <a.psi>    = a(u) = a0 + a1 u + a2 u^2,
+//   <a.psi v'> = V_x,     <a.psi e'> = kappa (theta a(u) + theta_x),  kappa = (K + dim - 1) / 2,
+// so a solve needs 1D moment sums of cubics only.  Bound by FP64 issue and by
+// the registers that set the number of waves: against the moment vectors of
+// psi the stage-1 interface sweep executes 4,541 instead of 5,618 flop per
+// point and holds 180 instead of 246 VGPRs, stage 2 132 instead of 246 (three
+// waves per SIMD): 1.54 and 1.14 ms against 1.55 and 1.40 ms at 2048^2.
+template <class FT> struct PSlope {
+  FT r, u, v, th;  // rho_x / rho, U_x, V_x, theta_x
+};
+// Constants of a state shared by its terms.
+template <class FT> struct PState {
+  FT U, V, th, ith, k2, hE;  // theta, 1 / theta, V^2 / 2, kappa theta + V^2 / 2
+};
+template <class FT, int DIM> FDK_HD PState<FT> pstate(const Prim<FT>& s, FT kappa) {
+  PState<FT> q;
+  q.U = s.U;
+  q.V = s.V;
+  q.th = s.i2l;
+  q.ith = FT(2) * s.lam;
+  q.hE = kappa * s.i2l;
+  if (DIM == 2) {
+    q.k2 = FT(0.5) * s.V * s.V;
+    q.hE = q.hE + q.k2;
+  } else {
+    q.k2 = FT(0);
+  }
+  return q;
+}
+// Slopes of the primitive variables from the derivative d of the conservative ones.
+template <class FT, int DIM> FDK_HD PSlope<FT> prim_slope(const Prim<FT>& s, FT g1, const FT* d) {
+  PSlope<FT> o;
+  o.r = d[0] * s.irho;
+  o.u = d[1] * s.irho - s.U * o.r;
+  if (DIM == 2) {
+    o.v = d[2] * s.irho - s.V * o.r;
+    const FT k2 = FT(0.5) * (s.U * s.U + s.V * s.V);
+    const FT e = d[3] * s.irho - k2 * o.r - s.U * o.u - s.V * o.v;  // (p_x / rho) / (gamma - 1)
+    o.th = g1 * e - s.i2l * o.r;
+  } else {
+    o.v = FT(0);
+    const FT e = d[2] * s.irho - FT(0.5) * s.U * s.U * o.r - s.U * o.u;
+    o.th = g1 * e - s.i2l * o.r;
+  }
+  return o;
+}
+// Euler time derivatives of the primitive variables from the normal slope a and the tangential slope b.
+template <class FT, int DIM>
+FDK_HD PSlope<FT> euler_slope(const PState<FT>& q, FT g1, const PSlope<FT>& a, const PSlope<FT>& b) {
+  PSlope<FT> t;
+  if (DIM == 2) {
+    const FT div = a.u + b.v;
+    t.r = -(div + q.U * a.r + q.V * b.r);
+    t.u = -(a.th + q.th * a.r + q.U * a.u + q.V * b.u);
+    t.v = -(b.th + q.th * b.r + q.U * a.v + q.V * b.v);
+    t.th = -(g1 * q.th * div + q.U * a.th + q.V * b.th);
+  } else {
+    t.r = -(a.u + q.U * a.r);
+    t.u = -(a.th + q.th * a.r + q.U * a.u);
+    t.v = FT(0);
+    t.th = -(g1 * q.th * a.u + q.U * a.th);
+  }
+  return t;
+}
+// a(u) of a slope
+template <class FT> FDK_HD void slope_poly(const PState<FT>& q, const PSlope<FT>& a, FT* o) {
+  const FT ux = a.u * q.ith;
+  o[2] = FT(0.5) * a.th * (q.ith * q.ith);
+  o[1] = ux - FT(2) * q.U * o[2];
+  o[0] = a.r - q.th * o[2] - q.U * (o[1] + q.U * o[2]);
+}
+// The terms of one state (a side over its half line, or the equilibrium over
+// the full line) that k0 + kA A.psi + kg ((a.psi) u + (b.psi) v) weights:
+// polynomials and the 1D moments common to the values and their time
+// derivatives.
+template <class FT, int DIM> struct PTerms {
+  FT A[3], g[4];         // A(u); (a.psi) u + (b.psi) v integrated over v', xi
+  FT vt[2], ng[2];       // weight v' (2D) with u^0, u^1: of A.psi, of the transport term
+  FT et[2], eg[2];       // weight V v' + e' beyond hE times weight 1
+};
+template <class FT, int DIM>
+FDK_HD PTerms<FT, DIM> pterms(const PState<FT>& q, FT kappa, const PSlope<FT>& a, const PSlope<FT>& b,
+                              const PSlope<FT>& t, const FT* mu) {
+  PTerms<FT, DIM> o;
+  FT pa[3];
+  slope_poly(q, a, pa);
+  slope_poly(q, t, o.A);
+  if (DIM == 2) {
+    FT pb[3];
+    slope_poly(q, b, pb);
+    o.g[0] = b.v + q.V * pb[0];
+    o.g[1] = pa[0] + q.V * pb[1];
+    o.g[2] = pa[1] + q.V * pb[2];
+    o.g[3] = pa[2];
+    const FT n0 = b.th + q.V * b.v + q.th * pb[0], n1 = a.v + q.th * pb[1], n2 = q.th * pb[2];
+    const FT e0 = q.th * b.v + kappa * (q.V * b.th), e1 = kappa * a.th;
+    const FT ett = kappa * t.th + q.V * t.v;
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+      o.vt[n] = t.v * mu[n];
+      o.ng[n] = n0 * mu[n] + n1 * mu[n + 1] + n2 * mu[n + 2];
+      o.et[n] = ett * mu[n];
+      o.eg[n] = e0 * mu[n] + e1 * mu[n + 1] + q.V * o.ng[n];
+    }
+  } else {
+    o.g[0] = FT(0);
+    o.g[1] = pa[0];
+    o.g[2] = pa[1];
+    o.g[3] = pa[2];
+    const FT e1 = kappa * a.th, ett = kappa * t.th;
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+      o.vt[n] = o.ng[n] = FT(0);
+      o.et[n] = ett * mu[n];
+      o.eg[n] = e1 * mu[n + 1];
+    }
+  }
+  return o;
+}
+// Adds the moments <psi (..)> to W and <u psi (..)> to F for one set of
+// coefficients (F[0] = W[1] is left to the caller).
+template <class FT, int DIM>
+FDK_HD void padd(const PState<FT>& q, const PTerms<FT, DIM>& p, const FT* mu, FT k0, FT kA, FT kg, FT* W, FT* F) {
+  const FT p0 = DIM == 2 ? k0 + kA * p.A[0] + kg * p.g[0] : k0 + kA * p.A[0];
+  const FT p1 = kA * p.A[1] + kg * p.g[1], p2 = kA * p.A[2] + kg * p.g[2], p3 = kg * p.g[3];
+  FT M[4];
+#pragma unroll
+  for (int n = 0; n < 4; ++n) M[n] = p0 * mu[n] + p1 * mu[n + 1] + p2 * mu[n + 2] + p3 * mu[n + 3];
+  W[0] = W[0] + M[0];
+  W[1] = W[1] + M[1];
+  F[1] = F[1] + M[2];
+  if (DIM == 2) {
+    W[2] = W[2] + q.V * M[0] + kA * p.vt[0] + kg * p.ng[0];
+    F[2] = F[2] + q.V * M[1] + kA * p.vt[1] + kg * p.ng[1];
+  }
+  W[DIM + 1] = W[DIM + 1] + FT(0.5) * M[2] + q.hE * M[0] + kA * p.et[0] + kg * p.eg[0];
+  F[DIM + 1] = F[DIM + 1] + FT(0.5) * M[3] + q.hE * M[1] + kA * p.et[1] + kg * p.eg[1];
+}
+// Conservative time derivative of a state from the primitive one
+template <class FT, int DIM> FDK_HD void cons_t(const Prim<FT>& s, FT hK, const PSlope<FT>& t, FT* Wt) {
+  const FT rt = s.rho * t.r;
+  Wt[0] = rt;
+  Wt[1] = s.rho * t.u + s.U * rt;
+  if (DIM == 2) {
+    Wt[2] = s.rho * t.v + s.V * rt;
+    Wt[3] = s.U * Wt[1] + s.V * Wt[2] + hK * (s.rho * t.th) + (hK * s.i2l - FT(0.5) * (s.U * s.U + s.V * s.V)) * rt;
+  } else {
+    Wt[2] = s.U * Wt[1] + hK * (s.rho * t.th) + (hK * s.i2l - FT(0.5) * s.U * s.U) * rt;
+  }
+}
+// One state's contribution to the moments of f^n (VALUES) and f_t^n.
+// mu[0], mu[1] given; the higher ones follow from the recursion.  ca: k0, kA,
+// kg of f^n, cb: of f_t^n.  t receives the Euler time derivatives.
+template <class FT, int DIM, bool VALUES>
+FDK_HD void pstate_terms(const Prim<FT>& s, FT kappa, FT g1, FT m0, FT m1, const FT* n, const FT* tang, const FT* ca,
+                         const FT* cb, FT* We, FT* F, FT* Wet, FT* Ft, PSlope<FT>& t) {
+  const PState<FT> q = pstate<FT, DIM>(s, kappa);
+  const PSlope<FT> a = prim_slope<FT, DIM>(s, g1, n);
+  PSlope<FT> b{};
+  if (DIM == 2) b = prim_slope<FT, DIM>(s, g1, tang);
+  t = euler_slope<FT, DIM>(q, g1, a, b);
+  FT mu[7];
+  mu[0] = m0;
+  mu[1] = m1;
+  mu_rec(mu, s.U, s.i2l);
+  const PTerms<FT, DIM> p = pterms<FT, DIM>(q, kappa, a, b, t, mu);
+  if (VALUES) padd<FT, DIM>(q, p, mu, s.rho * ca[0], s.rho * ca[1], s.rho * ca[2], We, F);
+  padd<FT, DIM>(q, p, mu, s.rho * cb[0], s.rho * cb[1], s.rho * cb[2], Wet, Ft);
+}
+
+template <class FT, int DIM, bool VALUES>
+FDK_HD void gks_iface(const Consts& k, FT dt, GksIO<FT, DIM>& io) {
+  if constexpr (!std::is_same_v<FT, double>) {
+    gks_iface_moments<FT, DIM, VALUES>(k, dt, io);
+    return;
+  }
+  constexpr int N = DIM + 2;
+  const FT K = FT(k.K), gam = FT(k.gamma), g1 = gam - FT(1);
+  const FT kappa = FT(0.5) * (K + FT(DIM - 1)), hK = FT(0.5) * (K + FT(DIM));
+  const Prim<FT> sL = prim<FT, DIM>(io.WL, gam), sR = prim<FT, DIM>(io.WR, gam);
+  // half-line moments <1> and x = <u> - U <1> of both sides, and the
+  // compatibility state W0: a half line holds the share <1> of its state's W,
+  // plus rho x of momentum and rho x U / 2 of energy
+  FT mL, mR, xL, xR, W0[N];
+  half_moms(sL, FT(1), mL, xL);
+  half_moms(sR, FT(-1), mR, xR);
+  {
+    const FT XL = sL.rho * xL, XR = sR.rho * xR;
+#pragma unroll
+    for (int i = 0; i < N; ++i) W0[i] = mL * io.WL[i] + mR * io.WR[i];
+    W0[1] = W0[1] + (XL + XR);
+    W0[N - 1] = W0[N - 1] + FT(0.5) * (sL.U * XL + sR.U * XR);
+  }
+  const Prim<FT> s0 = prim<FT, DIM>(W0, gam);
+  // collision time and time coefficients
+  const FT tau = (k.mu > 0 ? FT(k.mu) * s0.ip : FT(k.tau_c1) * dt) +
+                 FT(k.tau_c2) * dt * m_abs(sL.p - sR.p) / (sL.p + sR.p);
+  const TimeCoef<FT> tc = time_coef(dt, tau);
+  FT We[N], F[N], Wet[N], Ft[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) { We[i] = FT(0); F[i] = FT(0); Wet[i] = FT(0); Ft[i] = FT(0); }
+  PSlope<FT> tL, tR, t0;
+  {
+    // equilibrium part: slopes from the averaged normal slope (D12) and the
+    // tangential slope, time slope from compatibility
+    FT nm[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) nm[i] = FT(0.5) * (io.nL[i] + io.nR[i]);
+    // the leading terms (g0 itself) are W0 and its Euler flux, exact to the last
+    // operation; the polynomials carry the slope terms only
+    const FT H = W0[N - 1] + s0.p;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const FT fe = i == N - 1 ? s0.U * H : (i == 0 ? W0[1] : (i == 1 ? s0.p + s0.U * W0[1] : s0.V * W0[1]));
+      if (VALUES) { We[i] = tc.c[0] * W0[i]; F[i] = tc.c[0] * fe; }
+      Wet[i] = tc.ct[0] * W0[i];
+      Ft[i] = tc.ct[0] * fe;
+    }
+    const FT ca[3] = {FT(0), tc.c[2], tc.c[1]}, cb[3] = {FT(0), tc.ct[2], tc.ct[1]};
+    pstate_terms<FT, DIM, VALUES>(s0, kappa, g1, FT(1), s0.U, nm, io.Wt, ca, cb, We, F, Wet, Ft, t0);
+  }
+  {
+    // non-equilibrium initial parts of both sides: c3 (1 - tau A.psi) + c4 (...)
+    const FT ca[3] = {tc.c[3], -tau * tc.c[3], tc.c[4]}, cb[3] = {tc.ct[3], -tau * tc.ct[3], tc.ct[4]};
+    pstate_terms<FT, DIM, VALUES>(sL, kappa, g1, mL, sL.U * mL + xL, io.nL, io.Wt, ca, cb, We, F, Wet, Ft, tL);
+    pstate_terms<FT, DIM, VALUES>(sR, kappa, g1, mR, sR.U * mR + xR, io.nR, io.Wt, ca, cb, We, F, Wet, Ft, tR);
+  }
+  F[0] = We[1];
+  Ft[0] = Wet[1];
+  // Prandtl-number correction of the energy flux: (1/Pr - 1) times the heat
+  // flux 1/2 <(u-U0)((u-U0)^2 + (v-V0)^2 + xi^2)> of the same distribution,
+  // written with the moments of psi and u psi.
+  if (k.mu > 0) {
+    const FT U = s0.U, V = s0.V, f = FT(k.prfix);
+    if (DIM == 2) {
+      const FT a = FT(1.5) * U * U + FT(0.5) * V * V, b = FT(0.5) * U * (U * U + V * V), UV = U * V;
+      if (VALUES) F[3] = F[3] + f * (F[3] - U * F[1] - V * F[2] + a * F[0] - U * We[3] + UV * We[2] - b * We[0]);
+      Ft[3] = Ft[3] + f * (Ft[3] - U * Ft[1] - V * Ft[2] + a * Ft[0] - U * Wet[3] + UV * Wet[2] - b * Wet[0]);
+    } else {
+      const FT a = FT(1.5) * U * U, b = FT(0.5) * U * U * U;
+      if (VALUES) F[2] = F[2] + f * (F[2] - U * F[1] + a * F[0] - U * We[2] - b * We[0]);
+      Ft[2] = Ft[2] + f * (Ft[2] - U * Ft[1] + a * Ft[0] - U * Wet[2] - b * Wet[0]);
+    }
+  }
+  // interface values (Eq. W-model) with the one-sided Euler time derivatives
+  const FT e = tc.e1, oe = FT(1) - tc.e1;
+  FT WtL[N], WtR[N];
+  cons_t<FT, DIM>(sL, hK, tL, WtL);
+  cons_t<FT, DIM>(sR, hK, tR, WtR);
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    io.Ft[i] = Ft[i];
+    io.Wlt[i] = oe * Wet[i] + e * WtL[i];
+    io.Wrt[i] = oe * Wet[i] + e * WtR[i];
+    if (VALUES) {
+      io.F[i] = F[i];
+      io.Wl[i] = oe * We[i] + e * io.WL[i];
+      io.Wr[i] = oe * We[i] + e * io.WR[i];
+    }
+  }
+}
+
 // ------------------------------------------------ smooth nodal solver
 // f^n = g [1 - tauN ((a.psi) u + (b.psi) v + A.psi)], f_t = (A.psi) g.
 // Outputs x-flux F, Ft and (2D) y-flux G, Gt.  VALUES = false: F, G skipped.
 template <class FT, int DIM, bool VALUES>
-FDK_HD void gks_node(const Consts& k, const FT* W, const FT* Wx, const FT* Wy, FT* F, FT* Ft,
-                                         FT* G, FT* Gt) {
+FDK_HD void gks_node_moments(const Consts& k, const FT* W, const FT* Wx, const FT* Wy, FT* F, FT* Ft, FT* G, FT* Gt) {
   constexpr int N = DIM + 2;
   const FT K = FT(k.K), iKd = FT(k.inv_Kd);
   Prim<FT> s = prim<FT, DIM>(W, FT(k.gamma));
@@ -765,6 +1063,74 @@ FDK_HD void gks_node(const Consts& k, const FT* W, const FT* Wx, const FT* Wy, F
       FT q = F[2] - U * F[1] + a1 * F[0] - U * W[2] - b1 * W[0];
       FT qt = Ft[2] - U * Ft[1] + a1 * Ft[0] - U * Wt2 - b1 * Wt0;
       F[2] += f * q; Ft[2] += f * qt;
+    }
+  }
+}
+
+// The same in closed form (FP64): a Maxwellian's fluxes are the Euler fluxes
+// (their time derivative follows from the Euler equations), and the tau term
+// is the Navier-Stokes stress and heat flux of the BGK model, whose mass part
+// vanishes by compatibility.
+template <class FT, int DIM, bool VALUES>
+FDK_HD void gks_node(const Consts& k, const FT* W, const FT* Wx, const FT* Wy, FT* F, FT* Ft, FT* G, FT* Gt) {
+  if constexpr (!std::is_same_v<FT, double>) {
+    gks_node_moments<FT, DIM, VALUES>(k, W, Wx, Wy, F, Ft, G, Gt);
+    return;
+  }
+  const FT g1 = FT(k.gamma) - FT(1), hK = FT(0.5) * (FT(k.K) + FT(DIM)), h1 = hK + FT(1);
+  const Prim<FT> s = prim<FT, DIM>(W, FT(k.gamma));
+  const PState<FT> q = pstate<FT, DIM>(s, FT(0));
+  const PSlope<FT> a = prim_slope<FT, DIM>(s, g1, Wx);
+  PSlope<FT> b{};
+  if (DIM == 2) b = prim_slope<FT, DIM>(s, g1, Wy);
+  const PSlope<FT> t = euler_slope<FT, DIM>(q, g1, a, b);
+  FT Wt[DIM + 2];
+  cons_t<FT, DIM>(s, hK, t, Wt);
+  const bool visc = k.mu > 0;
+  const FT tp = visc ? FT(k.mu) : FT(0), f = FT(k.prfix);  // tau p = mu
+  const FT pt = s.rho * t.th + s.i2l * Wt[0];              // p_t
+  const FT H = W[DIM + 1] + s.p, Ht = Wt[DIM + 1] + pt;    // rho H and its time derivative
+  Ft[0] = Wt[1];
+  Ft[1] = pt + s.U * Wt[1] + W[1] * t.u;
+  Ft[DIM + 1] = s.U * Ht + t.u * H;
+  if (DIM == 2) {
+    Ft[2] = s.V * Wt[1] + W[1] * t.v;
+    Gt[0] = Wt[2];
+    Gt[1] = Ft[2];
+    Gt[2] = pt + s.V * Wt[2] + W[2] * t.v;
+    Gt[3] = s.V * Ht + t.v * H;
+  }
+  if (visc) {  // Prandtl correction of f_t: its heat flux about the node's velocity
+    Ft[DIM + 1] = Ft[DIM + 1] + f * (h1 * s.p * t.u);
+    if (DIM == 2) Gt[3] = Gt[3] + f * (h1 * s.p * t.v);
+  }
+  if (VALUES) {
+    F[0] = W[1];
+    F[1] = s.p + s.U * W[1];
+    F[DIM + 1] = s.U * H;
+    if (DIM == 2) {
+      F[2] = s.V * W[1];
+      G[0] = W[2];
+      G[1] = F[2];
+      G[2] = s.p + s.V * W[2];
+      G[3] = s.V * H;
+    }
+    if (visc) {
+      const FT kap = tp * h1 * (FT(1) + f);  // heat conductivity of the corrected flux
+      if (DIM == 2) {
+        const FT div = g1 * (a.u + b.v);
+        const FT sxx = tp * (FT(2) * a.u - div), syy = tp * (FT(2) * b.v - div), sxy = tp * (b.u + a.v);
+        F[1] = F[1] - sxx;
+        F[2] = F[2] - sxy;
+        F[3] = F[3] - (s.U * sxx + s.V * sxy + kap * a.th);
+        G[1] = G[1] - sxy;
+        G[2] = G[2] - syy;
+        G[3] = G[3] - (s.U * sxy + s.V * syy + kap * b.th);
+      } else {
+        const FT sxx = tp * (FT(2) * a.u - g1 * a.u);
+        F[1] = F[1] - sxx;
+        F[2] = F[2] - (s.U * sxx + kap * a.th);
+      }
     }
   }
 }
