@@ -245,10 +245,7 @@ __device__ __forceinline__ void edge_recon(const double* __restrict__ S, const G
         X[c][m] = x[m * st];
       }
     }
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-      rec[c] = fdk::recon_iface(k, Q[c][0], Q[c][1], Q[c][2], Q[c][3], X[c][0], X[c][1], X[c][2], X[c][3], g.h,
-                                g.invh);
+    fdk::recon_line<4>(k, Q, X, g.h, g.invh, rec);
   }
 }
 
@@ -382,20 +379,23 @@ __device__ __forceinline__ void node_derivs(const double* __restrict__ B, const 
   } else {
     // the stencil is loaded before the first reconstruction (one wait for
     // memory rather than one per component and axis)
-    double w[4][5], x[4][3], y[4][3];
+    double wx[4][3], wy[4][3], x[4][3], y[4][3], dx[4], dy[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       const double* pw = B + c * pl + o;
       const double* px = B + (4 + c) * pl + o;
       const double* py = B + (8 + c) * pl + o;
-      w[c][0] = pw[-1], w[c][1] = pw[0], w[c][2] = pw[1], w[c][3] = pw[-g.pitch], w[c][4] = pw[g.pitch];
+      wx[c][0] = pw[-1], wx[c][1] = pw[0], wx[c][2] = pw[1];
+      wy[c][0] = pw[-g.pitch], wy[c][1] = wx[c][1], wy[c][2] = pw[g.pitch];
       x[c][0] = px[-1], x[c][1] = px[0], x[c][2] = px[1];
       y[c][0] = py[-g.pitch], y[c][1] = py[0], y[c][2] = py[g.pitch];
     }
+    fdk::recon_node_line<4>(k, wx, x, g.h, g.invh, dx);
+    fdk::recon_node_line<4>(k, wy, y, g.h, g.invh, dy);
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-      Wx[c] = (FT)fdk::recon_node(k, w[c][0], w[c][1], w[c][2], x[c][0], x[c][1], x[c][2], g.h, g.invh);
-      Wy[c] = (FT)fdk::recon_node(k, w[c][3], w[c][1], w[c][4], y[c][0], y[c][1], y[c][2], g.h, g.invh);
+      Wx[c] = (FT)dx[c];
+      Wy[c] = (FT)dy[c];
     }
   }
 }
@@ -941,7 +941,7 @@ __device__ __forceinline__ int opaque_lane(int x) {
 }
 
 template <int STAGE, class FT, bool CHAR>
-__global__ __launch_bounds__(256, 2) void k_fused2d(const double* __restrict__ S, const double* __restrict__ Nb,
+__global__ __launch_bounds__(256, STAGE == 2 ? 3 : 2) void k_fused2d(const double* __restrict__ S, const double* __restrict__ Nb,
                                                     const double* __restrict__ Ain, double* __restrict__ Out,
                                                     double* __restrict__ Aout, Geo g_in, Consts k_in,
                                                     Scal* __restrict__ sc, double* __restrict__ part, int nparts,
@@ -1194,14 +1194,22 @@ __device__ void stage1d_block(double* __restrict__ S, const double* __restrict__
         io.Wt[c] = FT(0);
       }
     } else {
+      double Q[3][4], X[3][4];
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+          Q[c][m] = B[c * pl + at(g, 0, j - 1 + m)];
+          X[c][m] = B[(3 + c) * pl + at(g, 0, j - 1 + m)];
+        }
+      fdk::IfaceRec r[3];
+      fdk::recon_line<3>(k, Q, X, g.h, g.invh, r);
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
-        const double* w = B + c * pl + at(g, 0, j - 1);
-        const double* x = B + (3 + c) * pl + at(g, 0, j - 1);
-        fdk::IfaceRec r = fdk::recon_iface(k, w[0], w[1], w[2], w[3], x[0], x[1], x[2], x[3], g.h, g.invh);
-        io.WL[c] = (FT)r.vl; io.WR[c] = (FT)r.vr; io.nL[c] = (FT)r.dl; io.nR[c] = (FT)r.dr; io.Wt[c] = FT(0);
-        if (c == 0) chi = fmin(r.cl, r.cr);
+        io.WL[c] = (FT)r[c].vl; io.WR[c] = (FT)r[c].vr; io.nL[c] = (FT)r[c].dl; io.nR[c] = (FT)r[c].dr;
+        io.Wt[c] = FT(0);
       }
+      chi = fmin(r[0].cl, r[0].cr);
     }
     fdk::gks_iface<FT, 1, STAGE == 1>(k, (FT)dt, io);
     double* e = E + (long)l * 19 * pl + at(g, 0, j);
@@ -1240,12 +1248,19 @@ __device__ void stage1d_block(double* __restrict__ S, const double* __restrict__
         Wx[c] = (FT)d[c];
       }
     } else {
+      double Q[3][3], X[3][3], d[3];
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+#pragma unroll
+        for (int m = 0; m < 3; ++m) {
+          Q[c][m] = B[c * pl + at(g, 0, j - 1 + m)];
+          X[c][m] = B[(3 + c) * pl + at(g, 0, j - 1 + m)];
+        }
+      fdk::recon_node_line<3>(k, Q, X, g.h, g.invh, d);
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
-        const double* w = B + c * pl + at(g, 0, j);
-        const double* x = B + (3 + c) * pl + at(g, 0, j);
-        W[c] = (FT)w[0];
-        Wx[c] = (FT)fdk::recon_node(k, w[-1], w[0], w[1], x[-1], x[0], x[1], g.h, g.invh);
+        W[c] = (FT)Q[c][1];
+        Wx[c] = (FT)d[c];
       }
     }
     fdk::gks_node<FT, 1, STAGE == 1>(k, W, Wx, (const FT*)nullptr, F, Ft, (FT*)nullptr, (FT*)nullptr);
@@ -2042,7 +2057,7 @@ void launch_fused(fdcgks_problem* pb, const double* Sin, const double* Ain, doub
   const int nstrips = ceil_div(g.nx, FS_W);
   int rows = pb->fused_rows;
   if (rows <= 0) {
-    const int nch = std::max(1, 2 * pb->ncu / nstrips);
+    const int nch = std::max(1, (STAGE == 2 ? 3 : 2) * pb->ncu / nstrips);
     rows = std::max(16, ceil_div(g.ny, nch));
   }
   rows = std::min(rows, g.ny);
@@ -2268,6 +2283,7 @@ void setup_geometry(const fdcgks_params& prm, Geo& g, Consts& k) {
   k.tau_c1 = p->tau_c1;
   k.tau_c2 = p->tau_c2;
   k.r = p->geno_r;
+  k.geno_ratio = fdk::geno_smooth_ratio(k.C, k.inv_tanhC, k.r, k.eps);
   k.variant = p->flux_variant;
   k.grad_carried = p->grad_update == FDCGKS_GRAD_CARRIED;
   k.flux_order = p->flux_order;
@@ -3226,6 +3242,7 @@ fdcgks_status fdcgks_batch_create(int32_t count, const fdcgks_params* params, vo
   k.tau_c1 = p.tau_c1;
   k.tau_c2 = p.tau_c2;
   k.r = p.geno_r;
+  k.geno_ratio = fdk::geno_smooth_ratio(k.C, k.inv_tanhC, k.r, k.eps);
   k.variant = p.flux_variant;
   k.grad_carried = p.grad_update == FDCGKS_GRAD_CARRIED;
   k.flux_order = p.flux_order;

@@ -192,16 +192,16 @@ __global__ __launch_bounds__(EDGE_THREADS, FDCGKS3D_EDGE_WAVES) void k_edges3d(C
 #pragma unroll
       for (int m = 0; m < 4; ++m) { Q[cc][m] = W[at[m]]; X[cc][m] = Xp[at[m]]; }
     }
+    fdk::IfaceRec rec[5];
+    fdk::recon_line<5>(k, Q, X, g.h, g.invh, rec);
 #pragma unroll
     for (int cc = 0; cc < 5; ++cc) {
-      fdk::IfaceRec r = fdk::recon_iface<double>(k, Q[cc][0], Q[cc][1], Q[cc][2], Q[cc][3], X[cc][0], X[cc][1],
-                                                 X[cc][2], X[cc][3], g.h, g.invh);
-      xs[cc][t] = r.vl;
-      xs[5 + cc][t] = r.vr;
-      xs[10 + cc][t] = r.dl;
-      xs[15 + cc][t] = r.dr;
-      if (cc == 0) chi = fdk::g_min(r.cl, r.cr);
+      xs[cc][t] = rec[cc].vl;
+      xs[5 + cc][t] = rec[cc].vr;
+      xs[10 + cc][t] = rec[cc].dl;
+      xs[15 + cc][t] = rec[cc].dr;
     }
+    chi = fdk::g_min(rec[0].cl, rec[0].cr);
   }
   wave_sync();
   // phase 2: inputs in the local frame; the local v and w are the velocities
@@ -295,17 +295,15 @@ __global__ __launch_bounds__(NODE_BLOCK, FDCGKS3D_NODE_WAVES) void k_nodes3d(Con
     }
     // the axis's 25 stencil values are loaded before the first reconstruction,
     // so a wave waits for memory once per axis rather than once per component
-    double Wm[5], Wq[5], Xm[5], X0[5], Xq[5];
+    double Q[5][3], X[5][3];
 #pragma unroll
     for (int cc = 0; cc < 5; ++cc) {
       const double* Wp = Sg + (long)cc * g.n;
-      const double* X = Sg + (long)(5 * (1 + ax) + cc) * g.n;
-      Wm[cc] = Wp[am]; Wq[cc] = Wp[ap];
-      Xm[cc] = X[am]; X0[cc] = X[cell]; Xq[cc] = X[ap];
+      const double* Xp = Sg + (long)(5 * (1 + ax) + cc) * g.n;
+      Q[cc][0] = Wp[am]; Q[cc][1] = W[cc]; Q[cc][2] = Wp[ap];
+      X[cc][0] = Xp[am]; X[cc][1] = Xp[cell]; X[cc][2] = Xp[ap];
     }
-#pragma unroll
-    for (int cc = 0; cc < 5; ++cc)
-      D[ax][cc] = fdk::recon_node<double>(k, Wm[cc], W[cc], Wq[cc], Xm[cc], X0[cc], Xq[cc], g.h, g.invh);
+    fdk::recon_node_line<5>(k, Q, X, g.h, g.invh, D[ax]);
   }
   double F[3][5], Ft[3][5];
   fdk3::gks_node<VALUES>(k, W, D[0], D[1], D[2], F, Ft);
@@ -564,6 +562,7 @@ void setup(const fdcgks3d_params& p, Geo3& g, Consts& k) {
   k.tau_c1 = p.tau_c1;
   k.tau_c2 = p.tau_c2;
   k.r = p.geno_r;
+  k.geno_ratio = fdk::geno_smooth_ratio(k.C, k.inv_tanhC, k.r, k.eps);
   k.variant = p.flux_variant;
   k.grad_carried = p.grad_update == FDCGKS_GRAD_CARRIED;
   k.flux_order = p.flux_order;

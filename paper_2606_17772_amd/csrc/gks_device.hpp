@@ -26,6 +26,7 @@ struct Consts {
   double prfix;       // 1/Pr - 1 (applied when mu > 0)
   double C, inv_tanhC, eps, eps_a, dc, ds;  // GENO (Sec. 3.2, App. D)
   double tau_c1, tau_c2;
+  double geno_ratio;  // smooth-data bound on tau / (smallest indicator + eps), see geno_smooth_ratio (0: not used)
   int r;              // GENO exponent
   int variant;        // 0: (6-4), 1: (6-2), 2: linear
   int grad_carried;
@@ -43,6 +44,74 @@ FDK_HD double m_abs(double x) { return fabs(x); }
 FDK_HD float m_abs(float x) { return fabsf(x); }
 
 template <class T> FDK_HD T sqr(T a) { return a * a; }
+
+// Reciprocal and square root of normal numbers: Newton steps on the hardware
+// estimates without the scaling and fix-up of the IEEE sequences (5 and 8
+// instructions instead of about 11 and 18; results within an ulp).  Not for
+// arguments that may be zero, denormal or infinite.
+template <class T> FDK_HD T m_recip(T x) { return T(1) / x; }
+FDK_HD double m_recip(double x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  double r = __builtin_amdgcn_rcp(x);
+  r = __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);
+  return __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);
+#else
+  return 1.0 / x;
+#endif
+}
+FDK_HD double m_sqrt_normal(double x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const double y = __builtin_amdgcn_rsq(x);
+  double g = x * y, h = 0.5 * y;
+  double d = __builtin_fma(-h, g, 0.5);
+  g = __builtin_fma(g, d, g);
+  h = __builtin_fma(h, d, h);
+  d = __builtin_fma(-g, g, x);
+  return __builtin_fma(d, h, g);
+#else
+  return sqrt(x);
+#endif
+}
+// exp(-x) and 1 - exp(-x) for x >= 0, both to the last digits: -x = k ln 2 + r,
+// expm1(r) = r + r^2 (1/2 + r q(r)) with q interpolated at Chebyshev nodes of
+// |r| <= ln(2) / 2 (relative error of exp below 8e-17 before rounding).
+FDK_HD void exp_neg(double x, double& E, double& one_minus_E) {
+  const double y = fmin(x, 800.0);  // exp(-800) = 0; a NaN argument comes with NaN states
+  const double k = __builtin_rint(-y * 1.4426950408889634);
+  double r = __builtin_fma(k, -0x1.62e42fefa3000p-1, -y);
+  r = __builtin_fma(k, -0x1.3de6af278ece6p-42, r);
+  double q = 0x1.af238498b289ap-26;
+  q = __builtin_fma(q, r, 0x1.2880562d283e2p-22);
+  q = __builtin_fma(q, r, 0x1.71de17dab6782p-19);
+  q = __builtin_fma(q, r, 0x1.a019c99634817p-16);
+  q = __builtin_fma(q, r, 0x1.a01a01a4b5021p-13);
+  q = __builtin_fma(q, r, 0x1.6c16c17393002p-10);
+  q = __builtin_fma(q, r, 0x1.1111111110e69p-7);
+  q = __builtin_fma(q, r, 0x1.5555555554cb2p-5);
+  q = __builtin_fma(q, r, 0x1.5555555555555p-3);
+  q = __builtin_fma(q, r, 0.5);
+  const double m = __builtin_fma(r * r, q, r);  // expm1(r)
+  const double s = ldexp(1.0, (int)k);
+  E = __builtin_fma(s, m, s);
+  one_minus_E = __builtin_fma(-s, m, 1.0 - s);
+}
+// erf(z) / 2 for |z| <= 1: z p(z^2), p interpolated at Chebyshev nodes of [0, 1] (relative error below 5e-17).
+FDK_HD double half_erf_small(double z) {
+  const double t = z * z;
+  double p = -0x1.ac9585a44fe29p-32;
+  p = __builtin_fma(p, t, 0x1.d76af6ca49787p-28);
+  p = __builtin_fma(p, t, -0x1.5c131500d3f88p-24);
+  p = __builtin_fma(p, t, 0x1.b981d78881a5dp-21);
+  p = __builtin_fma(p, t, -0x1.f4ca838adb73bp-18);
+  p = __builtin_fma(p, t, 0x1.f9a2be4f731a1p-15);
+  p = __builtin_fma(p, t, -0x1.c02db0665e53dp-12);
+  p = __builtin_fma(p, t, 0x1.565bccfa44156p-9);
+  p = __builtin_fma(p, t, -0x1.b82ce31203772p-7);
+  p = __builtin_fma(p, t, 0x1.ce2f21a040f66p-5);
+  p = __builtin_fma(p, t, -0x1.812746b0379c1p-3);
+  p = __builtin_fma(p, t, 0x1.20dd750429b6dp-1);
+  return z * p;
+}
 
 template <class T> FDK_HD T ipow(T x, int r) {
   T y = x;
@@ -69,6 +138,23 @@ FDK_HD float val(float a) { return a; }
 template <class R> struct GenoOutT {
   R v, d, chi;
 };
+// Largest ratio x = tau / (ISL + eps) below which the path function saturates
+// whatever the other indicators are: alpha = 2 aH / (aH + aL) with aH >= 1 is at
+// least 2 / (2 + x^r), so C alpha >= 19.5 (1 + 1e-12) where x^r <= beta =
+// 2 C / (19.5 (1 + 1e-12)) - 2.  0 (never) where 1 / tanh(C) is not 1, beta is
+// not positive or eps does not keep the quotients normal.
+inline double geno_smooth_ratio(double C, double inv_tanhC, int r, double eps) {
+  const double beta = 2.0 * C / (19.5 * (1.0 + 1e-12)) - 2.0;
+  if (inv_tanhC != 1.0 || !(beta > 0.0) || !(eps >= 1e-100)) return 0.0;
+  return std::pow(beta, 1.0 / r) * (1.0 - 1e-9);
+}
+// Smooth data decided from one ratio: where it holds (and IS1, hence every
+// indicator, is far from overflow) geno() returns PH, PHx and chi = 1.
+template <class R> FDK_HD bool geno_smooth(const Consts& k, R IS1, R IS2, R IS3) {
+  const R tau = 0.5 * g_abs((IS2 + IS3) - 2.0 * IS1);
+  const R eL = g_min(IS1, g_min(IS2, IS3)) + k.eps;
+  return val(tau) < k.geno_ratio * val(eL) && val(IS1) <= 1e100;
+}
 template <class R>
 FDK_HD GenoOutT<R> geno(const Consts& k, R IS1, R IS2, R IS3, double d1, double d2, double d3,
                                             R q1, R q2, R q3, R dq1, R dq2, R dq3, R PH, R PHx) {
@@ -168,6 +254,51 @@ FDK_HD IfaceRecT<R> recon_iface(const Consts& k, R q0, R q1, R q2, R q3, R x0, R
   return o;
 }
 
+// The same where both sides pass the one-ratio smooth test (or the scheme is
+// linear): returns whether they do; o then holds recon_iface's result.
+FDK_HD bool recon_iface_smooth(const Consts& k, double q0, double q1, double q2, double q3, double x0, double x1,
+                               double x2, double x3, double h, double invh, IfaceRec& o) {
+  const double PHl = ((7.0 * q0 + 35.0 * q1 + 21.0 * q2 + q3) + (x0 + 22.0 * x1 - 7.0 * x2) * h) * (1.0 / 64.0);
+  const double PHr = ((q0 + 21.0 * q1 + 35.0 * q2 + 7.0 * q3) + (7.0 * x1 - 22.0 * x2 - x3) * h) * (1.0 / 64.0);
+  const double PHx = -((q0 + 45.0 * q1 - 45.0 * q2 - q3) + 9.0 * (x1 + x2) * h) * (invh * (1.0 / 30.0));
+  o.vl = PHl; o.dl = PHx; o.cl = 1.0;
+  o.vr = PHr; o.dr = PHx; o.cr = 1.0;
+  if (k.variant == 2) return true;
+  const double hx0 = h * x0, hx3 = h * x3;
+  const double D2 = sqr(q0 - 2.0 * q1 + q2), D3 = sqr(q1 - 2.0 * q2 + q3);
+  const double ISl1 = (13.0 / 3.0) * sqr(q1 - q0 - hx0) + sqr(2.0 * (q1 - q0) - hx0);
+  const double ISl2 = (13.0 / 12.0) * D2 + 0.25 * sqr(q2 - q0);
+  const double ISl3 = (13.0 / 12.0) * D3 + 0.25 * sqr(3.0 * q1 - 4.0 * q2 + q3);
+  const double ISr1 = (13.0 / 3.0) * sqr(q2 - q3 + hx3) + sqr(2.0 * (q3 - q2) - hx3);
+  const double ISr2 = (13.0 / 12.0) * D3 + 0.25 * sqr(q3 - q1);
+  const double ISr3 = (13.0 / 12.0) * D2 + 0.25 * sqr(3.0 * q2 - 4.0 * q1 + q0);
+  // both tests evaluated, no branch between them
+  return (int)geno_smooth<double>(k, ISl1, ISl2, ISl3) & (int)geno_smooth<double>(k, ISr1, ISr2, ISr3);
+}
+// A line of N components: one straight run of arithmetic that is all of it on
+// smooth data, the general routine for components that are not smooth (the
+// results are recon_iface's bit for bit).  The general routine per component
+// and side cost two branches and about 15 more FP64 operations each, and the
+// scheduler could not mix the components.
+template <int N>
+FDK_HD void recon_line(const Consts& k, const double (&Q)[N][4], const double (&X)[N][4], double h, double invh,
+                       IfaceRec (&rec)[N]) {
+  bool ok[N], all = true;
+#pragma unroll
+  for (int c = 0; c < N; ++c) {
+    ok[c] = recon_iface_smooth(k, Q[c][0], Q[c][1], Q[c][2], Q[c][3], X[c][0], X[c][1], X[c][2], X[c][3], h, invh,
+                               rec[c]);
+    all = (int)all & (int)ok[c];
+  }
+  if (!all) {
+#pragma unroll
+    for (int c = 0; c < N; ++c)
+      if (!ok[c])
+        rec[c] = recon_iface<double>(k, Q[c][0], Q[c][1], Q[c][2], Q[c][3], X[c][0], X[c][1], X[c][2], X[c][3], h,
+                                     invh);
+  }
+}
+
 // Node derivative from q0..q2 = Q_{j-1..j+1}, x0..x2 (Eq. 6th-compact-recons,
 // App. C3; the central sub-stencil is the IS^tau reference with weight dc).
 template <class R>
@@ -183,6 +314,34 @@ FDK_HD R recon_node(const Consts& k, R q0, R q1, R q2, R x0, R x1, R x2, double 
   R dq3 = (q2 - q0) * (0.5 * invh);
   GenoOutT<R> o = geno<R>(k, IS3, IS1, IS2, k.dc, k.ds, k.ds, q1, q1, q1, dq3, dq1, dq2, q1, PHx);
   return o.d;
+}
+
+// The same, and whether the one-ratio smooth test holds.
+FDK_HD bool recon_node_smooth(const Consts& k, double q0, double q1, double q2, double x0, double x1, double x2,
+                              double h, double invh, double& d) {
+  d = (9.0 * (q0 - q2) + h * (x0 + 46.0 * x1 + x2)) * (invh * (1.0 / 30.0));
+  if (k.variant == 2) return true;
+  const double hx0 = h * x0, hx2 = h * x2;
+  const double IS1 = (13.0 / 3.0) * sqr(q1 - q0 - hx0) + sqr(2.0 * (q1 - q0) - hx0);
+  const double IS2 = (13.0 / 3.0) * sqr(q2 - q1 - hx2) + sqr(2.0 * (q2 - q1) - hx2);
+  const double IS3 = (13.0 / 12.0) * sqr(q0 - 2.0 * q1 + q2) + 0.25 * sqr(q2 - q0);
+  return geno_smooth<double>(k, IS3, IS1, IS2);
+}
+// Node derivatives of N components along one axis (as recon_line).
+template <int N>
+FDK_HD void recon_node_line(const Consts& k, const double (&Q)[N][3], const double (&X)[N][3], double h, double invh,
+                            double (&d)[N]) {
+  bool ok[N], all = true;
+#pragma unroll
+  for (int c = 0; c < N; ++c) {
+    ok[c] = recon_node_smooth(k, Q[c][0], Q[c][1], Q[c][2], X[c][0], X[c][1], X[c][2], h, invh, d[c]);
+    all = (int)all & (int)ok[c];
+  }
+  if (!all) {
+#pragma unroll
+    for (int c = 0; c < N; ++c)
+      if (!ok[c]) d[c] = recon_node<double>(k, Q[c][0], Q[c][1], Q[c][2], X[c][0], X[c][1], X[c][2], h, invh);
+  }
 }
 
 // ------------------------------------- characteristic variables (Sec. 3)
@@ -283,10 +442,7 @@ FDK_HD void recon_iface_char(const Consts& k, const double (&Q)[DIM + 2][4], con
     for (int c = 0; c < N; ++c) xc[c][m] = b[c];
   }
   IfaceRec cr[N];
-#pragma unroll
-  for (int c = 0; c < N; ++c)
-    cr[c] = recon_iface<double>(k, qc[c][0], qc[c][1], qc[c][2], qc[c][3], xc[c][0], xc[c][1], xc[c][2], xc[c][3],
-                                h, invh);
+  recon_line<N>(k, qc, xc, h, invh, cr);
   chi = fmin(fmin(cr[0].cl, cr[0].cr), fmin(cr[N - 1].cl, cr[N - 1].cr));
   double a[N], b[N];
 #pragma unroll
@@ -333,9 +489,7 @@ FDK_HD void recon_node_char(const Consts& k, const double (&Q)[DIM + 2][3], cons
     for (int c = 0; c < N; ++c) xc[c][m] = b[c];
   }
   double dc[N];
-#pragma unroll
-  for (int c = 0; c < N; ++c)
-    dc[c] = recon_node<double>(k, qc[c][0], qc[c][1], qc[c][2], xc[c][0], xc[c][1], xc[c][2], h, invh);
+  recon_node_line<N>(k, qc, xc, h, invh, dc);
   from_char<DIM>(f, dc, d);
 }
 
@@ -410,13 +564,13 @@ template <class FT> struct Prim {
 template <class FT, int DIM> FDK_HD Prim<FT> prim(const FT* W, FT gamma) {
   Prim<FT> s;
   s.rho = W[0];
-  s.irho = FT(1) / W[0];
+  s.irho = m_recip(W[0]);
   s.U = W[1] * s.irho;
   s.V = DIM == 2 ? W[2] * s.irho : FT(0);
   FT rE = W[DIM + 1];
   s.p = (gamma - FT(1)) * (rE - FT(0.5) * s.rho * (s.U * s.U + s.V * s.V));
   s.i2l = s.p * s.irho;          // 1/(2 lambda) = p/rho
-  s.ip = FT(1) / s.p;            // lambda = rho/(2p); 1/p also serves the collision time
+  s.ip = m_recip(s.p);           // lambda = rho/(2p); 1/p also serves the collision time
   s.lam = FT(0.5) * s.rho * s.ip;
   return s;
 }
@@ -433,11 +587,16 @@ template <class FT> FDK_HD void mom_full(const Prim<FT>& s, Mom<FT>& m) {
   mu_rec(m.mu, s.U, s.i2l);
 }
 // half line: sgn = +1 (u > 0) or -1 (u < 0); <1> and <u> - U <1>
-template <class FT> FDK_HD void half_moms(const Prim<FT>& s, FT sgn, FT& m0, FT& x) {
-  FT sl = m_sqrt(s.lam);
-  m0 = FT(0.5) * m_erfc(-sgn * sl * s.U);
+FDK_HD void half_moms(const Prim<double>& s, double sgn, double& m0, double& x) {
+  const double sl = m_sqrt_normal(s.lam), z = sl * s.U;
+  // |z| <= 1 up to a normal Mach number of about 1.2; a wave goes through the
+  // library's erfc only if one of its points is beyond
+  if (fabs(z) <= 1.0) m0 = 0.5 + sgn * half_erf_small(z);
+  else m0 = 0.5 * m_erfc(-sgn * z);
+  double E, o;
+  exp_neg(z * z, E, o);
   // 1/(2 sqrt(pi lambda)) = (1/(2 lambda)) sqrt(lambda) / sqrt(pi): no second square root
-  x = sgn * m_exp(-s.lam * s.U * s.U) * (s.i2l * sl) * FT(0.56418958354775628695);
+  x = sgn * E * (s.i2l * sl) * 0.56418958354775628695;
 }
 template <class FT> FDK_HD void mom_half(const Prim<FT>& s, FT sgn, Mom<FT>& m) {
   FT sl = m_sqrt(s.lam);
@@ -479,18 +638,17 @@ template <class FT> struct TimeCoef {
 };
 template <class FT> FDK_HD TimeCoef<FT> time_coef(FT dt, FT tau) {
   TimeCoef<FT> r;
-  // tau = 0 (p_l = p_r without a c1 term): the tau -> 0+ limit, exp(-T/tau) = 0
-  FT Eh = val(tau) > 0 ? m_exp(-FT(0.5) * dt / tau) : FT(0);
-  FT Ef = Eh * Eh;
-  r.e1 = Ef;
-  FT idt = FT(1) / dt;
   if constexpr (std::is_same_v<FT, double>) {
     // The fit written out: with s = tau / dt, E = exp(-dt / (2 tau)) and
     // o = 1 - E the ten combinations (4 q(dt/2) - q(dt)) / dt and
     // 4 (q(dt) - 2 q(dt/2)) / dt^2 of the integrals reduce to four numbers.
-    const FT s = tau * idt, o = FT(1) - Eh;
+    // tau = 0 (p_l = p_r without a c1 term): the tau -> 0+ limit, E = 0.
+    double Eh = 0.0, o = 1.0;
+    if (tau > 1e-290) exp_neg(0.5 * dt * m_recip(tau), Eh, o);
+    const FT idt = m_recip(dt), s = tau * idt;
+    r.e1 = Eh * Eh;
     const FT c3 = s * o * (FT(2) + o);
-    const FT c4 = tau * ((FT(2) * Eh - Ef) - FT(2) * c3);
+    const FT c4 = tau * ((FT(1) - o * o) - FT(2) * c3);  // 2 E - E^2 = 1 - o^2
     const FT t0 = FT(4) * s * (o * o), t1 = FT(4) * s * (o * (Eh - FT(2) * s * o));
     r.c[0] = FT(1) - c3;
     r.c[1] = -tau - c4;
@@ -504,6 +662,9 @@ template <class FT> FDK_HD TimeCoef<FT> time_coef(FT dt, FT tau) {
     r.ct[4] = -t1;
     return r;
   }
+  // tau = 0 (p_l = p_r without a c1 term): the tau -> 0+ limit, exp(-T/tau) = 0
+  FT Eh = val(tau) > 0 ? m_exp(-FT(0.5) * dt / tau) : FT(0);
+  FT Ef = Eh * Eh;
   FT Th = FT(0.5) * dt, Tf = dt;
   FT qh[5], qf[5];
   qh[0] = Th - tau * (FT(1) - Eh);
@@ -516,12 +677,14 @@ template <class FT> FDK_HD TimeCoef<FT> time_coef(FT dt, FT tau) {
   qf[3] = tau * (FT(1) - Ef);
   qh[4] = tau * ((Th + FT(2) * tau) * Eh - FT(2) * tau);
   qf[4] = tau * ((Tf + FT(2) * tau) * Ef - FT(2) * tau);
+  FT idt = FT(1) / dt;
   FT idt2 = FT(4) * idt * idt;
 #pragma unroll
   for (int k = 0; k < 5; ++k) {
     r.c[k] = (FT(4) * qh[k] - qf[k]) * idt;
     r.ct[k] = (qf[k] - FT(2) * qh[k]) * idt2;
   }
+  r.e1 = Ef;
   return r;
 }
 
@@ -889,11 +1052,7 @@ FDK_HD void pstate_terms(const Prim<FT>& s, FT kappa, FT g1, FT m0, FT m1, const
 }
 
 template <class FT, int DIM, bool VALUES>
-FDK_HD void gks_iface(const Consts& k, FT dt, GksIO<FT, DIM>& io) {
-  if constexpr (!std::is_same_v<FT, double>) {
-    gks_iface_moments<FT, DIM, VALUES>(k, dt, io);
-    return;
-  }
+FDK_HD void gks_iface_slopes(const Consts& k, FT dt, GksIO<FT, DIM>& io) {
   constexpr int N = DIM + 2;
   const FT K = FT(k.K), gam = FT(k.gamma), g1 = gam - FT(1);
   const FT kappa = FT(0.5) * (K + FT(DIM - 1)), hK = FT(0.5) * (K + FT(DIM));
@@ -914,7 +1073,7 @@ FDK_HD void gks_iface(const Consts& k, FT dt, GksIO<FT, DIM>& io) {
   const Prim<FT> s0 = prim<FT, DIM>(W0, gam);
   // collision time and time coefficients
   const FT tau = (k.mu > 0 ? FT(k.mu) * s0.ip : FT(k.tau_c1) * dt) +
-                 FT(k.tau_c2) * dt * m_abs(sL.p - sR.p) / (sL.p + sR.p);
+                 FT(k.tau_c2) * dt * m_abs(sL.p - sR.p) * m_recip(sL.p + sR.p);
   const TimeCoef<FT> tc = time_coef(dt, tau);
   FT We[N], F[N], Wet[N], Ft[N];
 #pragma unroll
@@ -978,6 +1137,12 @@ FDK_HD void gks_iface(const Consts& k, FT dt, GksIO<FT, DIM>& io) {
       io.Wr[i] = oe * We[i] + e * io.WR[i];
     }
   }
+}
+
+template <class FT, int DIM, bool VALUES>
+FDK_HD void gks_iface(const Consts& k, FT dt, GksIO<FT, DIM>& io) {
+  if constexpr (std::is_same_v<FT, double>) gks_iface_slopes<FT, DIM, VALUES>(k, dt, io);
+  else gks_iface_moments<FT, DIM, VALUES>(k, dt, io);
 }
 
 // ------------------------------------------------ smooth nodal solver
