@@ -43,12 +43,10 @@ constexpr int NNP = 30;   // node-flux planes per grid
 constexpr int EDGE_THREADS = 256;   // interface sweep block: four waves
 constexpr int EDGE_WAVE_POINTS = 21;  // interface points per wave (63 busy lanes, 3 solves per point)
 constexpr int EDGE_POINTS = 4 * EDGE_WAVE_POINTS;  // interface points per block
-// Minimum waves per SIMD of the interface and node sweeps.  Measured on a
-// 128^3 Navier-Stokes step: the interface sweep is fastest at 1 (about 440
-// registers, no spills; 2 waves spill 192 registers and take 40% longer),
-// the node sweep at 2 (17% faster than at 1).
+// Minimum waves per SIMD of the interface and node sweeps: the solver holds
+// 254 registers at stage 1, two waves (a point fewer would not buy a third).
 #ifndef FDCGKS3D_EDGE_WAVES
-#define FDCGKS3D_EDGE_WAVES 1
+#define FDCGKS3D_EDGE_WAVES 2
 #endif
 #ifndef FDCGKS3D_NODE_WAVES
 #define FDCGKS3D_NODE_WAVES 2
@@ -118,9 +116,9 @@ __device__ __forceinline__ void wave_sync() {
 // x-fastest order) and normal axis l % 3; lane 63 idles.  The three solves of
 // a point thus sit in neighbouring lanes of one wave, which exchange data
 // through LDS with wave-level ordering only (no block barrier, so a wave never
-// waits for the other waves of its block).  A block is four waves: the solver
-// needs about 440 registers, one wave per SIMD, and a four-wave block keeps all
-// four SIMDs of a compute unit busy (a three-wave block left one idle).
+// waits for the other waves of its block).  A block is four waves, one per
+// SIMD of a compute unit.  Bound by FP64 issue: at 128^3 the sweeps took 5.48
+// (stage 1) and 4.66 ms at one wave per SIMD with the moment-vector solver.
 // The axis varies across a wave, so every component permutation goes through
 // LDS (addresses are free to compute; registers cannot be indexed at run
 // time):

@@ -587,8 +587,8 @@ template <class FT> FDK_HD void mom_full(const Prim<FT>& s, Mom<FT>& m) {
   mu_rec(m.mu, s.U, s.i2l);
 }
 // half line: sgn = +1 (u > 0) or -1 (u < 0); <1> and <u> - U <1>
-FDK_HD void half_moms(const Prim<double>& s, double sgn, double& m0, double& x) {
-  const double sl = m_sqrt_normal(s.lam), z = sl * s.U;
+FDK_HD void half_moms(double lam, double i2l, double U, double sgn, double& m0, double& x) {
+  const double sl = m_sqrt_normal(lam), z = sl * U;
   // |z| <= 1 up to a normal Mach number of about 1.2; a wave goes through the
   // library's erfc only if one of its points is beyond
   if (fabs(z) <= 1.0) m0 = 0.5 + sgn * half_erf_small(z);
@@ -596,7 +596,7 @@ FDK_HD void half_moms(const Prim<double>& s, double sgn, double& m0, double& x) 
   double E, o;
   exp_neg(z * z, E, o);
   // 1/(2 sqrt(pi lambda)) = (1/(2 lambda)) sqrt(lambda) / sqrt(pi): no second square root
-  x = sgn * E * (s.i2l * sl) * 0.56418958354775628695;
+  x = sgn * E * (i2l * sl) * 0.56418958354775628695;
 }
 template <class FT> FDK_HD void mom_half(const Prim<FT>& s, FT sgn, Mom<FT>& m) {
   FT sl = m_sqrt(s.lam);
@@ -1061,8 +1061,8 @@ FDK_HD void gks_iface_slopes(const Consts& k, FT dt, GksIO<FT, DIM>& io) {
   // compatibility state W0: a half line holds the share <1> of its state's W,
   // plus rho x of momentum and rho x U / 2 of energy
   FT mL, mR, xL, xR, W0[N];
-  half_moms(sL, FT(1), mL, xL);
-  half_moms(sR, FT(-1), mR, xR);
+  half_moms(sL.lam, sL.i2l, sL.U, 1.0, mL, xL);
+  half_moms(sR.lam, sR.i2l, sR.U, -1.0, mR, xR);
   {
     const FT XL = sL.rho * xL, XR = sR.rho * xR;
 #pragma unroll
