@@ -64,6 +64,24 @@ int main() {
             }
             differ += std::memcmp(a, b, sizeof a) != 0;
             differ += std::memcmp(da, db, sizeof da) != 0;
+            // the forms that read the line again and evaluate both sides in one run
+            fdk::recon_line_compact<4>(
+                k, Q, X,
+                [&](int c, double (&q)[4], double (&x)[4]) {
+                  for (int m = 0; m < 4; ++m) { q[m] = Q[c][m]; x[m] = X[c][m]; }
+                },
+                h, invh, a);
+            fdk::recon_node_compact<4>(
+                k, Q3, X3,
+                [&](int c, double (&q)[3], double (&x)[3]) {
+                  for (int m = 0; m < 3; ++m) { q[m] = Q3[c][m]; x[m] = X3[c][m]; }
+                },
+                h, invh, da);
+            auto same = [](double u, double v) { return std::memcmp(&u, &v, sizeof u) == 0 || (u != u && v != v); };
+            for (int c = 0; c < 4; ++c)
+              differ += !(same(a[c].vl, b[c].vl) && same(a[c].dl, b[c].dl) && same(a[c].cl, b[c].cl) &&
+                          same(a[c].vr, b[c].vr) && same(a[c].dr, b[c].dr) && same(a[c].cr, b[c].cr) &&
+                          same(da[c], db[c]));
             // indicator triples over the whole double range
             double IS[3];
             for (int t = 0; t < 3; ++t) {
