@@ -2040,6 +2040,29 @@ __global__ __launch_bounds__(256) void k_bphase_update(BArgs a, Consts k) {
 __global__ void k_bphase_end(BArgs a, Consts k) { batch_step_end(a, k); }
 
 
+// ------------------------------------------------ state in and out
+// Every plane of one grid between its padded layout (base: the grid's first
+// plane at its first stored node, rows `pitch`, planes `plane` apart) and the
+// caller's fields (field f's planes f * ncomp .. at u[f], rows `row` apart, my
+// rows a plane): one launch.  Twelve 2D copies cost a launch each, 2.4 to 3 us
+// on the device and more on the host: half of a small gradient's time.
+struct DensePtrs {
+  double* u[3];
+};
+template <bool TO_STATE>
+__global__ __launch_bounds__(256) void k_state_io(double* __restrict__ base, long pitch, long plane, DensePtrs d, int ncomp,
+                                                  int mx, int my, long row) {
+  const int f = blockIdx.y / ncomp, c = blockIdx.y % ncomp;
+  double* u = (f == 0 ? d.u[0] : (f == 1 ? d.u[1] : d.u[2])) + (long)c * row * my;
+  double* p = base + (long)blockIdx.y * plane;
+  const long n = (long)mx * my;
+  for (long t = blockIdx.x * 256L + threadIdx.x; t < n; t += gridDim.x * 256L) {
+    const int j = (int)(t / mx), i = (int)(t - (long)j * mx);
+    if (TO_STATE) p[(long)j * pitch + i] = u[(long)j * row + i];
+    else u[(long)j * row + i] = p[(long)j * pitch + i];
+  }
+}
+
 // ------------------------------------------- allocation-free 1D run
 // fdcgks_step1d_static keeps every buffer of a 1D run in one file-scope
 // device array: the four state buffers (12 planes each), the interface
@@ -2174,6 +2197,36 @@ void free_all(fdcgks_problem* pb) {
 }
 
 int ceil_div(long a, long b) { return (int)((a + b - 1) / b); }
+
+// Whether a kernel of the current device may access `count` doubles at p:
+// memory of this device, managed or pinned, all inside one allocation.
+// Anything else handed over as a device pointer keeps to the runtime's copies.
+bool kernel_reaches(const void* p, size_t count) {
+  hipPointerAttribute_t at;
+  int dev = -1;
+  if (hipPointerGetAttributes(&at, p) != hipSuccess || hipGetDevice(&dev) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  if (at.type != hipMemoryTypeDevice || at.device != dev || !at.devicePointer || at.devicePointer != p) return false;
+  hipDeviceptr_t lo = nullptr;
+  size_t len = 0;
+  if (hipMemGetAddressRange(&lo, &len, (hipDeviceptr_t)p) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  const char* end = static_cast<const char*>(p) + count * sizeof(double);
+  return (reinterpret_cast<uintptr_t>(p) & 7) == 0 && end <= static_cast<const char*>(lo) + len;
+}
+// One grid's planes in or out (k_state_io); base: the grid's first plane.
+void launch_state_io(hipStream_t stream, const Geo& g, double* base, double* const* ptrs, int nfield, int ncomp, int mx,
+                     int my, long row, bool to_state) {
+  DensePtrs d{};
+  for (int f = 0; f < nfield; ++f) d.u[f] = ptrs[f];
+  const dim3 gr(std::min(ceil_div((long)mx * my, 256), 4096), nfield * ncomp);
+  hipLaunchKernelGGL((to_state ? k_state_io<true> : k_state_io<false>), gr, dim3(256), 0, stream,
+                     base + (long)OY * g.pitch + OX, (long)g.pitch, g.plane, d, ncomp, mx, my, row);
+}
 
 // Kernel classes reported by fdcgks_step_timed.
 enum { TK_HALO = 0, TK_EDGE1, TK_NODE1, TK_UPD1, TK_EDGE2, TK_NODE2, TK_UPD2, TK_STEP, TK_COUNT };
@@ -2725,30 +2778,32 @@ static fdcgks_status copy_grid(fdcgks_problem* pb, int grid, double* const* ptrs
   size_t row = (size_t)mx * sizeof(double), upitch = (size_t)row_stride * sizeof(double);
   if (!on_device && row_stride == mx) {
     // Dense host arrays: one contiguous host transfer per field through the
-    // interface buffer (idle between steps, 100 planes, room for the ncomp
-    // dense planes of a field), and the padded layout by device-to-device 2D
-    // copies.  Pageable 2D host copies row by row are several times slower.
-    double* stage = pb->E;
-    const size_t plane_dense = (size_t)mx * my, field_bytes = plane_dense * ncomp * sizeof(double);
-    for (int f = 0; f < nfield; ++f) {
-      double* dev0 = base + (long)f * ncomp * g.plane + (long)OY * g.pitch + OX;
-      if (to_device_state)
-        HIPCHK(pb, hipMemcpyAsync(stage, ptrs[f], field_bytes, hipMemcpyHostToDevice, pb->stream));
-      for (int c = 0; c < ncomp; ++c) {
-        double* dev = dev0 + (long)c * g.plane;
-        double* st = stage + (long)c * plane_dense;
-        if (to_device_state)
-          HIPCHK(pb, hipMemcpy2DAsync(dev, (size_t)g.pitch * sizeof(double), st, row, row, my,
-                                      hipMemcpyDeviceToDevice, pb->stream));
-        else
-          HIPCHK(pb, hipMemcpy2DAsync(st, row, dev, (size_t)g.pitch * sizeof(double), row, my,
-                                      hipMemcpyDeviceToDevice, pb->stream));
-      }
-      if (!to_device_state)
-        HIPCHK(pb, hipMemcpyAsync(ptrs[f], stage, field_bytes, hipMemcpyDeviceToHost, pb->stream));
-    }
+    // interface buffer (idle between steps, 100 planes, room for the grid's
+    // dense planes), and the padded layout by one launch.  Pageable 2D host
+    // copies row by row are several times slower.
+    const size_t field = (size_t)mx * my * ncomp;
+    double* stage[3];
+    for (int f = 0; f < nfield; ++f) stage[f] = pb->E + f * field;
+    if (to_device_state)
+      for (int f = 0; f < nfield; ++f)
+        HIPCHK(pb, hipMemcpyAsync(stage[f], ptrs[f], field * sizeof(double), hipMemcpyHostToDevice, pb->stream));
+    launch_state_io(pb->stream, g, base, stage, nfield, ncomp, mx, my, mx, to_device_state);
+    fdcgks_status st = launch_check(pb, "state copy");
+    if (st) return st;
+    if (!to_device_state)
+      for (int f = 0; f < nfield; ++f)
+        HIPCHK(pb, hipMemcpyAsync(ptrs[f], stage[f], field * sizeof(double), hipMemcpyDeviceToHost, pb->stream));
     HIPCHK(pb, hipStreamSynchronize(pb->stream));
     return FDCGKS_OK;
+  }
+  if (on_device) {
+    const size_t need = (size_t)row_stride * my * (ncomp - 1) + (size_t)row_stride * (my - 1) + mx;
+    bool ok = true;
+    for (int f = 0; f < nfield; ++f) ok = ok && kernel_reaches(ptrs[f], need);
+    if (ok) {
+      launch_state_io(pb->stream, g, base, ptrs, nfield, ncomp, mx, my, row_stride, to_device_state);
+      return launch_check(pb, "state copy");
+    }
   }
   hipMemcpyKind kind = to_device_state ? (on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice)
                                        : (on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost);
@@ -3128,27 +3183,41 @@ fdcgks_status fdcgks_step_vjp(fdcgks_problem* pb, double dt, const double* lam_o
   if (st) return st;
   const Geo& g = pb->g;
   const size_t pitchb = (size_t)g.pitch * sizeof(double);
-  const long interior = (long)OY * g.pitch + OX;
   // dense layout: grid 0's 12 planes, then grid 1's (one more node along a bounded axis)
   const int mx[2] = {g.nx, g.nx + g.sx}, my[2] = {g.ny, g.ny + g.sy};
   const long total = 12L * ((long)mx[0] * my[0] + (long)mx[1] * my[1]);
-  auto dense_plane = [&](int p) {  // offset of plane p (grid p / 12) in the dense layout
-    return p < 12 ? (long)p * mx[0] * my[0] : 12L * mx[0] * my[0] + (long)(p - 12) * mx[1] * my[1];
+  // both grids' planes between the padded layout and a dense array, one launch
+  // a grid; an array the kernels cannot reach goes plane by plane
+  auto planes = [&](double* padded, double* dense, bool in) -> fdcgks_status {
+    const bool direct = kernel_reaches(dense, (size_t)total);
+    for (int gr = 0; gr < 2; ++gr) {
+      const size_t n = (size_t)mx[gr] * my[gr], row = (size_t)mx[gr] * sizeof(double);
+      double* d = dense + (gr ? 12 * (size_t)mx[0] * my[0] : 0);
+      double* q = padded + 12L * gr * g.plane;
+      if (direct) {
+        double* const f[3] = {d, d + 4 * n, d + 8 * n};
+        launch_state_io(pb->stream, g, q, f, 3, 4, mx[gr], my[gr], mx[gr], in);
+        continue;
+      }
+      for (int p = 0; p < 12; ++p) {
+        double* pq = q + p * g.plane + (long)OY * g.pitch + OX;
+        if (in) HIPCHK(pb, hipMemcpy2DAsync(pq, pitchb, d + p * n, row, row, my[gr], hipMemcpyDeviceToDevice, pb->stream));
+        else HIPCHK(pb, hipMemcpy2DAsync(d + p * n, row, pq, pitchb, row, my[gr], hipMemcpyDeviceToDevice, pb->stream));
+      }
+    }
+    return launch_check(pb, "adjoint copy");
   };
   // adjoint of the step output into the padded layout (halo stays zero)
   // host input: one contiguous transfer into the interface buffer (written
   // by the forward recompute only after these copies, in stream order), then
-  // device-to-device 2D copies into the padded layout
-  const double* lsrc = lam_out;
+  // into the padded layout
+  double* lsrc = const_cast<double*>(lam_out);
   if (!on_device) {
     HIPCHK(pb, hipMemcpyAsync(pb->E, lam_out, (size_t)total * sizeof(double), hipMemcpyHostToDevice, pb->stream));
     lsrc = pb->E;
   }
-  for (int p = 0; p < 24; ++p) {
-    const size_t row = (size_t)mx[p / 12] * sizeof(double);
-    HIPCHK(pb, hipMemcpy2DAsync(pb->Lo + p * g.plane + interior, pitchb, lsrc + dense_plane(p), row, row,
-                                my[p / 12], hipMemcpyDeviceToDevice, pb->stream));
-  }
+  st = planes(pb->Lo, lsrc, true);
+  if (st) return st;
   // forward recompute at the frozen dt: stage-1 results into E1/Nb1, stage-2 into E/Nb
   std::memset(pb->sc_host, 0, sizeof(Scal));
   pb->sc_host->dt = dt;
@@ -3174,11 +3243,8 @@ fdcgks_status fdcgks_step_vjp(fdcgks_problem* pb, double dt, const double* lam_o
   // host output: dense through the interface buffer (free once the reverse
   // sweeps are done), then one contiguous transfer
   double* ldst = on_device ? lam_in : pb->E;
-  for (int p = 0; p < 24; ++p) {
-    const size_t row = (size_t)mx[p / 12] * sizeof(double);
-    HIPCHK(pb, hipMemcpy2DAsync(ldst + dense_plane(p), row, pb->LS0 + p * g.plane + interior, pitchb, row,
-                                my[p / 12], hipMemcpyDeviceToDevice, pb->stream));
-  }
+  st = planes(pb->LS0, ldst, false);
+  if (st) return st;
   if (!on_device) {
     HIPCHK(pb, hipMemcpyAsync(lam_in, pb->E, (size_t)total * sizeof(double), hipMemcpyDeviceToHost, pb->stream));
     HIPCHK(pb, hipStreamSynchronize(pb->stream));
@@ -3561,13 +3627,22 @@ static fdcgks_status batch_copy(fdcgks_batch* b, int m, int grid, double* const*
   const size_t dense = (size_t)mx * my;
   // host arrays go through the member's interface buffer (idle between
   // steps) as one contiguous transfer per field, like single problems
+  double* stage[3];
+  bool direct = true;
   for (int f = 0; f < 3; ++f) {
-    double* stage = on_device ? ptrs[f] : b->mem[m].E;
-    if (to_dev && !on_device)
-      BHIPCHK(b, hipMemcpyAsync(stage, ptrs[f], 4 * dense * sizeof(double), hipMemcpyHostToDevice, b->stream));
-    for (int c = 0; c < 4; ++c) {
-      double* dev = base + (long)(f * 4 + c) * g.plane + (long)OY * g.pitch + OX;
-      double* usr = stage + (long)c * dense;
+    stage[f] = on_device ? ptrs[f] : b->mem[m].E + f * 4 * dense;
+    direct = direct && (!on_device || kernel_reaches(stage[f], 4 * dense));
+  }
+  if (to_dev && !on_device)
+    for (int f = 0; f < 3; ++f)
+      BHIPCHK(b, hipMemcpyAsync(stage[f], ptrs[f], 4 * dense * sizeof(double), hipMemcpyHostToDevice, b->stream));
+  if (direct) {
+    launch_state_io(b->stream, g, base, stage, 3, 4, mx, my, mx, to_dev);
+    BHIPCHK(b, hipGetLastError());
+  } else {
+    for (int q = 0; q < 12; ++q) {
+      double* dev = base + (long)q * g.plane + (long)OY * g.pitch + OX;
+      double* usr = stage[q / 4] + (long)(q % 4) * dense;
       if (to_dev)
         BHIPCHK(b, hipMemcpy2DAsync(dev, (size_t)g.pitch * sizeof(double), usr, row, row, my,
                                     hipMemcpyDeviceToDevice, b->stream));
@@ -3575,9 +3650,10 @@ static fdcgks_status batch_copy(fdcgks_batch* b, int m, int grid, double* const*
         BHIPCHK(b, hipMemcpy2DAsync(usr, row, dev, (size_t)g.pitch * sizeof(double), row, my,
                                     hipMemcpyDeviceToDevice, b->stream));
     }
-    if (!to_dev && !on_device)
-      BHIPCHK(b, hipMemcpyAsync(ptrs[f], stage, 4 * dense * sizeof(double), hipMemcpyDeviceToHost, b->stream));
   }
+  if (!to_dev && !on_device)
+    for (int f = 0; f < 3; ++f)
+      BHIPCHK(b, hipMemcpyAsync(ptrs[f], stage[f], 4 * dense * sizeof(double), hipMemcpyDeviceToHost, b->stream));
   if (!on_device) BHIPCHK(b, hipStreamSynchronize(b->stream));
   return FDCGKS_OK;
 }

@@ -103,3 +103,35 @@ def test_strided_copies(bounded):
             assert np.all(o[..., nx_g:] == 0.0)
     with pytest.raises(FdcgksError, match="row_stride"):
         pb.set_state(0, *(np.zeros(4 * ny * nx) for _ in range(3)), row_stride=nx - 1)
+
+
+@pytest.mark.parametrize("nx,ny,bounded", [(4, 4, False), (65, 33, False), (300, 7, True), (37, 130, True)])
+def test_device_arrays_in_and_out(nx, ny, bounded):
+    """Device arrays (dense, with padded rows, and views that start at any
+    element) give the state host arrays give, on both grids."""
+    import torch
+
+    from paper_2606_17772_amd import Problem, make_params
+    kw = {"sides": ("no_slip", "zero_gradient", "reflecting", "reflecting")} if bounded else {}
+    pb = Problem(make_params(dim=2, nx=nx, ny=ny, lx=1.0, **kw))
+    rng = np.random.default_rng(nx)
+    for g in range(2):
+        shape = pb.grid_shape(g)
+        F = [rng.standard_normal(shape) for _ in range(3)]
+        n = F[0].size
+        flat = torch.zeros(3 * n + 1, dtype=torch.float64, device="cuda:0")
+        flat[1:] = torch.from_numpy(np.concatenate([f.ravel() for f in F])).to("cuda:0")
+        pb.set_state(g, *(flat[1 + q * n:1 + (q + 1) * n] for q in range(3)))  # 8-byte aligned only
+        for a, b in zip(pb.get_state(g), F):
+            assert np.array_equal(a, b)
+        for a, b in zip(pb.get_state(g, device="cuda:0"), F):
+            assert np.array_equal(a.cpu().numpy(), b)
+        # padded rows on the device
+        ry, rx = pb.grid_dims(g)
+        rs = rx + 5
+        P = [torch.full((shape[0], ry, rs), 7.0, dtype=torch.float64, device="cuda:0") for _ in range(3)]
+        for q in range(3):
+            P[q][:, :, :rx] = torch.from_numpy(F[(q + 1) % 3]).to("cuda:0")
+        pb.set_state(g, *(p.reshape(-1) for p in P), row_stride=rs)
+        for q, a in enumerate(pb.get_state(g)):
+            assert np.array_equal(a, F[(q + 1) % 3])
