@@ -536,7 +536,7 @@ __global__ __launch_bounds__(256) void k_adj_nodes(const double* __restrict__ S,
   }
 }
 
-// Transpose of the halo fill (k_halo_rows, then k_halo_cols): a ghost value
+// Transpose of the halo fill (k_halo): a ghost value
 // fac * P[src] hands its adjoint to its source, columns first (their ghost
 // rows included), then rows.  Stored node coordinates, as the state planes.
 __global__ void k_adj_fold_cols(double* __restrict__ L, int nplanes, Geo g) {

@@ -117,42 +117,66 @@ __device__ __forceinline__ PlaneInfo plane_info(const Geo& g, int p) {
   q.my = g.ny + (q.dual ? g.sy : 0);
   return q;
 }
-__global__ void k_halo_rows(double* __restrict__ S, int nplanes, Geo g, const Scal* __restrict__ sc) {
+// Every ghost from its real source in one launch: ghost rows over all columns
+// (corners included: the column rule of the row rule's value, as filling rows
+// first and whole columns after would give them), then ghost columns of the
+// real rows.
+__global__ __launch_bounds__(256) void k_halo(double* __restrict__ S, int nplanes, Geo g, const Scal* __restrict__ sc) {
   if (sc->stop) return;
-  const int W = g.nx + g.sx;
-  long n = (long)nplanes * 2 * HALO * W;
+  const int W = g.nx + g.sx + 2 * HALO, H = g.ny + g.sy;
+  const long per = 2L * HALO * W + 2L * HALO * H, n = (long)nplanes * per;
   for (long t = blockIdx.x * (long)blockDim.x + threadIdx.x; t < n; t += (long)gridDim.x * blockDim.x) {
-    int i = (int)(t % W);
-    long r = t / W;
-    int hr = (int)(r % (2 * HALO));
-    int p = (int)(r / (2 * HALO));
+    const int p = (int)(t / per);
+    int r = (int)(t - p * per);
     const PlaneInfo q = plane_info(g, p);
-    if (i >= q.mx) continue;
-    int j = hr < HALO ? hr - HALO : q.my + (hr - HALO);
-    double fac;
-    int js = ghost_src(j, q.my, g.side[2], g.side[3], q.dual && g.sy, q.field == 2, q.comp == 2,
-                       q.comp == 1 || q.comp == 2, fac);
+    int i, j;
+    if (r < 2 * HALO * W) {
+      const int hr = r / W;
+      i = r - hr * W - HALO;
+      j = hr < HALO ? hr - HALO : q.my + (hr - HALO);
+      if (i >= q.mx + HALO) continue;
+    } else {
+      r -= 2 * HALO * W;
+      j = r / (2 * HALO);
+      const int hc = r - j * 2 * HALO;
+      i = hc < HALO ? hc - HALO : q.mx + (hc - HALO);
+      if (j >= q.my) continue;
+    }
+    double fy = 1.0, fx = 1.0;
+    int js = j, is = i;
+    if (j < 0 || j >= q.my)
+      js = ghost_src(j, q.my, g.side[2], g.side[3], q.dual && g.sy, q.field == 2, q.comp == 2, q.comp == 1 || q.comp == 2,
+                     fy);
+    if (i < 0 || i >= q.mx)
+      is = ghost_src(i, q.mx, g.side[0], g.side[1], q.dual && g.sx, q.field == 1, q.comp == 1, q.comp == 1 || q.comp == 2,
+                     fx);
     double* P = S + p * g.plane;
-    P[at(g, j, i)] = fac * P[at(g, js, i)];
+    P[at(g, j, i)] = fx * (fy * P[at(g, js, is)]);
   }
 }
-__global__ void k_halo_cols(double* __restrict__ S, int nplanes, Geo g, const Scal* __restrict__ sc) {
-  if (sc->stop) return;
-  int rows = g.ny + g.sy + 2 * HALO;
-  long n = (long)nplanes * rows * 2 * HALO;
-  for (long t = blockIdx.x * (long)blockDim.x + threadIdx.x; t < n; t += (long)gridDim.x * blockDim.x) {
-    int hc = (int)(t % (2 * HALO));
-    long r = t / (2 * HALO);
-    int j = (int)(r % rows) - HALO;
-    int p = (int)(r / rows);
-    const PlaneInfo q = plane_info(g, p);
-    if (j >= q.my + HALO) continue;
-    int i = hc < HALO ? hc - HALO : q.mx + (hc - HALO);
-    double fac;
-    int is = ghost_src(i, q.mx, g.side[0], g.side[1], q.dual && g.sx, q.field == 1, q.comp == 1,
-                       q.comp == 1 || q.comp == 2, fac);
-    double* P = S + p * g.plane;
-    P[at(g, j, i)] = fac * P[at(g, j, is)];
+
+// The ghosts that copy node i of an axis of n real nodes (the inverse of
+// ghost_src): fn(ghost index, factor) for each.
+template <class F>
+__device__ __forceinline__ void for_images(int i, int n, int lo, int hi, bool on_line, bool normal_deriv, bool odd_refl,
+                                           bool odd_noslip, const F& fn) {
+#pragma unroll 1
+  for (int side = 0; side < 2; ++side) {
+    const int d = side == 0 ? i : n - 1 - i;  // distance from the side's end node
+    if (d > HALO) continue;
+    const int type = side == 0 ? lo : hi, out = side == 0 ? -1 : 1;
+    if (type == FDCGKS_BC_PERIODIC) {
+      if (d < HALO) fn(i - out * n, 1.0);  // the image beyond the other end
+      continue;
+    }
+    if (type == FDCGKS_BC_ZERO_GRADIENT) {
+      if (d == 0)
+        for (int r = 1; r <= HALO; ++r) fn(i + out * r, normal_deriv ? 0.0 : 1.0);
+      continue;
+    }
+    const bool odd = type == FDCGKS_BC_NO_SLIP ? odd_noslip : odd_refl;
+    const int r = on_line ? d : d + 1;  // the mirror image's distance beyond the end node
+    if (r >= 1 && r <= HALO) fn((side == 0 ? 0 : n - 1) + out * r, odd != normal_deriv ? -1.0 : 1.0);
   }
 }
 
@@ -487,21 +511,27 @@ __device__ __forceinline__ int wall_mask(const Geo& g, int grid, int i, int j) {
   return zero;
 }
 
-template <int STAGE, class NF, bool WIDE = false>
-__device__ __forceinline__ void update_node(const double* __restrict__ S, const double* __restrict__ E,
-                                            const NF& nf, const double* __restrict__ Ain, double* __restrict__ Out,
-                                            double* __restrict__ Aout, const Geo& g, const Consts& k, double dt,
-                                            int i, int j, int grid, Scal* sc, int member, bool want_cfl,
-                                            double& cfl_s, double& cfl_r) {
+// The new conservative values of a node (the squares of the momenta summed in
+// component order), and W, x and y derivative of the component done last.
+struct NewNode {
+  double rho = 0.0, mom2 = 0.0, ener = 0.0, mU = 0.0, mV = 0.0, W, GX, GY;
+};
+
+// Components c0 .. c1 - 1 of node (i, j): the new values and derivatives, stored
+// in Out; stage 1 also stores the accumulators.
+template <int STAGE, class NF, bool WIDE>
+__device__ __forceinline__ void update_comps(const double* __restrict__ S, const double* __restrict__ E, const NF& nf,
+                                             const double* __restrict__ Ain, double* __restrict__ Out,
+                                             double* __restrict__ Aout, const Geo& g, const Consts& k, double dt, int i,
+                                             int j, int grid, int c0, int c1, NewNode& v) {
   const long pl = g.plane, o = at(g, j, i);
   const int r = grid;
   const long so = o + (grid ? g.dshift : 0);  // the dual planes are shifted along bounded axes
   const double* s = S + (long)grid * 12 * pl + so;
   double* out = Out + (long)grid * 12 * pl + so;
   const int zero = wall_mask(g, grid, i, j);
-  double rho = 0.0, mom2 = 0.0, ener = 0.0, mU = 0.0, mV = 0.0;  // the new values
 #pragma unroll FDCGKS_UPDATE_UNROLL
-  for (int c = 0; c < 4; ++c) {
+  for (int c = c0; c < c1; ++c) {
     double L = 0.0, Lt = 0.0, Gr[2], Grt[2];
 #pragma unroll
     for (int a = 0; a < 2; ++a) {
@@ -568,18 +598,28 @@ __device__ __forceinline__ void update_node(const double* __restrict__ S, const 
     __builtin_nontemporal_store((double)(W), &out[c * pl]);
     __builtin_nontemporal_store((double)(GX), &out[(4 + c) * pl]);
     __builtin_nontemporal_store((double)(GY), &out[(8 + c) * pl]);
-    if (c == 0) rho = W;
-    else if (c == 3) ener = W;
+    if (c == 0) v.rho = W;
+    else if (c == 3) v.ener = W;
     else {
-      mom2 = mom2 + W * W;
-      if (c == 1) mU = W;
-      else mV = W;
+      v.mom2 = v.mom2 + W * W;
+      if (c == 1) v.mU = W;
+      else v.mV = W;
     }
+    v.W = W;
+    v.GX = GX;
+    v.GY = GY;
   }
+}
+
+// The checks of a node's new values, and its share of the next time step.
+template <int STAGE>
+__device__ __forceinline__ void update_check(const NewNode& v, const Consts& k, int i, int j, int grid, Scal* sc, int member,
+                                             bool want_cfl, double& cfl_s, double& cfl_r) {
+  const double rho = v.rho, ener = v.ener, mom2 = v.mom2;
   if (want_cfl) {
     // wave speed and density of the new state, written as the CFL reduction
     // (k_cfl_partial) writes them, so the next step's dt is bit for bit the same
-    const double U = mU / rho, V = mV / rho;
+    const double U = v.mU / rho, V = v.mV / rho;
     const double pc = (k.gamma - 1.0) * (ener - 0.5 * rho * (U * U + V * V));
     const double c = sqrt(k.gamma * pc / rho);
     cfl_s = fmax(fabs(U), fabs(V)) + c;
@@ -595,6 +635,17 @@ __device__ __forceinline__ void update_node(const double* __restrict__ S, const 
       sc->fail_stage = STAGE;
     }
   }
+}
+
+template <int STAGE, class NF, bool WIDE = false>
+__device__ __forceinline__ void update_node(const double* __restrict__ S, const double* __restrict__ E,
+                                            const NF& nf, const double* __restrict__ Ain, double* __restrict__ Out,
+                                            double* __restrict__ Aout, const Geo& g, const Consts& k, double dt,
+                                            int i, int j, int grid, Scal* sc, int member, bool want_cfl,
+                                            double& cfl_s, double& cfl_r) {
+  NewNode v;
+  update_comps<STAGE, NF, WIDE>(S, E, nf, Ain, Out, Aout, g, k, dt, i, j, grid, 0, 4, v);
+  update_check<STAGE>(v, k, i, j, grid, sc, member, want_cfl, cfl_s, cfl_r);
 }
 
 // Nodal fluxes from the node buffer (planes grid*16 + a*8 + q).
@@ -731,6 +782,86 @@ __global__ __launch_bounds__(256, (STAGE == 2 ? 5 : 4) - (WIDE ? 1 : 0)) void k_
   if (fold) cfl_fold(part, nparts, s, r);
 }
 
+
+// --------------------------------------------------- joined launches
+// The unfused stage in two launches.  A small problem's stage is bound by its
+// launches (4 to 5 us each from the start to the end of the shortest) and by
+// the latency of single waves: so the two sweeps share one, and the update
+// runs a thread per component (a node's four components wait for memory at
+// once instead of one after the other) and writes the ghosts that copy its
+// nodes, so that no halo launch follows it.  A large problem's is bound by
+// bandwidth either way.  Per step against halo, interface, node and update
+// launches of their own: 96x48 39 against 70 us, 256^2 periodic 100 against
+// 126, zero gradient 153 against 183, 512^2 308 against 343, 1024^2 1143
+// against 1154, 2048^2 zero gradient 5.18 against 5.17 ms.
+template <int STAGE, class FT, bool CHAR>
+__global__ __launch_bounds__(128, FDCGKS_EDGE_WAVES) void k_sweeps2d(const double* __restrict__ S, double* __restrict__ E,
+                                                                     double* __restrict__ Nb, Geo g, Consts k,
+                                                                     const Scal* __restrict__ sc, int etx, int ent, int epad,
+                                                                     int ntx, int nnt, int npad) {
+  if (sc->stop) return;  // grid-uniform
+  int id = blockIdx.x, t;
+  if (id < 2 * epad) {  // interface tiles of family 0, then 1; everything here is block-uniform
+    const int fam = id >= epad;
+    if (!xcd_tile(id - fam * epad, epad, ent, t)) return;
+    edge_block<STAGE, FT, CHAR>(S, E, g, k, sc->dt, t % etx, t / etx, fam, -OX);
+  } else {
+    id -= 2 * epad;
+    const int grid = id >= npad;
+    if (!xcd_tile(id - grid * npad, npad, nnt, t)) return;
+    node_block<STAGE, FT, CHAR>(S, Nb, g, k, t % ntx, t / ntx, grid, node_reach(k), -OX);
+  }
+}
+
+template <int STAGE, bool WIDE>
+__global__ __launch_bounds__(256) void k_update_comps2d(const double* __restrict__ S, const double* __restrict__ E,
+                                                        const double* __restrict__ Nb, const double* __restrict__ Ain,
+                                                        double* __restrict__ Out, double* __restrict__ Aout, Geo g, Consts k,
+                                                        Scal* __restrict__ sc, double* __restrict__ part, int nparts) {
+  if (sc->stop) return;  // grid-uniform
+  __shared__ double sW[4][64];
+  const int grid = blockIdx.z, c = threadIdx.y, tx = threadIdx.x;
+  const int i = blockIdx.x * 64 + tx - (grid ? g.sx : 0), j = blockIdx.y - (grid ? g.sy : 0);
+  const bool mine = i < g.nx && j < g.ny;
+  if (mine) {
+    const NodeFluxGlobal nf{Nb + (long)grid * 16 * g.plane + at(g, j, i), g.plane, g.pitch};
+    NewNode v;
+    update_comps<STAGE, NodeFluxGlobal, WIDE>(S, E, nf, Ain, Out, Aout, g, k, sc->dt, i, j, grid, c, c + 1, v);
+    sW[c][tx] = v.W;
+    // ghosts, in stored node coordinates
+    const int si = i + (grid ? g.sx : 0), sj = j + (grid ? g.sy : 0);
+    const int mx = g.nx + (grid ? g.sx : 0), my = g.ny + (grid ? g.sy : 0);
+    if (si <= HALO || sj <= HALO || si >= mx - 1 - HALO || sj >= my - 1 - HALO) {
+#pragma unroll 1
+      for (int f = 0; f < 3; ++f) {
+        const double val = f == 0 ? v.W : (f == 1 ? v.GX : v.GY);
+        double* P = Out + (long)(grid * 12 + f * 4 + c) * g.plane;
+        auto row = [&](int gj, double vy, bool real) {  // row gj holds vy at column si
+          if (!real) P[at(g, gj, si)] = vy;
+          for_images(si, mx, g.side[0], g.side[1], grid && g.sx, f == 1, c == 1, c == 1 || c == 2,
+                     [&](int gi, double fx) { P[at(g, gj, gi)] = fx * vy; });
+        };
+        row(sj, val, true);
+        for_images(sj, my, g.side[2], g.side[3], grid && g.sy, f == 2, c == 2, c == 1 || c == 2,
+                   [&](int gj, double fy) { row(gj, fy * val, false); });
+      }
+    }
+  }
+  __syncthreads();
+  if (c != 0) return;
+  double cfl_s = 0.0, cfl_r = 1e300;
+  if (mine) {
+    NewNode v;
+    v.rho = sW[0][tx];
+    v.mU = sW[1][tx];
+    v.mV = sW[2][tx];
+    v.ener = sW[3][tx];
+    v.mom2 = v.mom2 + v.mU * v.mU;
+    v.mom2 = v.mom2 + v.mV * v.mV;
+    update_check<STAGE>(v, k, i, j, grid, sc, 0, STAGE == 2 && part, cfl_s, cfl_r);
+  }
+  if (STAGE == 2 && part) cfl_fold(part, nparts, cfl_s, cfl_r);
+}
 
 // ------------------------------------ interface sweep fused with the update
 // Periodic problems with the order-6 flux.  A block of 64 x 4 threads owns a
@@ -1747,8 +1878,9 @@ __global__ __launch_bounds__(256) void k_diag_partial(const double* __restrict__
 
 // Start of a step: dt from the partials (or the fixed dt), clipped to t_end;
 // sets the "done" bit when t has reached t_end.
+// advance: first the end of the step before (as k_step_end).
 __global__ void k_step_begin(double* __restrict__ part, int nparts, Scal* __restrict__ sc, double cfl,
-                             double h, double mu, int use_cfl) {
+                             double h, double mu, int use_cfl, int advance) {
   __shared__ double smax[256], smin[256];
   double vmax = 0.0, rmin = 1e300;
   if (use_cfl)
@@ -1771,6 +1903,10 @@ __global__ void k_step_begin(double* __restrict__ part, int nparts, Scal* __rest
   }
   if (threadIdx.x == 0) {
     if (sc->stop) return;
+    if (advance) {
+      sc->t += sc->dt;
+      sc->steps += 1;
+    }
     double dt;
     if (use_cfl) {
       dt = cfl * h / smax[0];
@@ -1873,8 +2009,8 @@ __device__ __forceinline__ void cfl_block(const BArgs& a, const Consts& k, const
 }
 
 // Halo of state plane p of a member (rows over the real columns, then whole
-// columns): periodic images or the ghosts of bounded sides, as k_halo_rows /
-// k_halo_cols fill them for a single problem.
+// columns): periodic images or the ghosts of bounded sides, as k_halo fills
+// them for a single problem.
 __device__ __forceinline__ void halo_plane_block(double* __restrict__ S, const Geo& g, int p) {
   const int nthr = blockDim.x * blockDim.y, tid = threadIdx.y * blockDim.x + threadIdx.x;
   const PlaneInfo q = plane_info(g, p);
@@ -2146,6 +2282,7 @@ struct fdcgks_problem {
   // launch shapes of the interface, node and update kernels (x, y threads):
   // fdcgks_autotune's pick on the 2048^2 shear layer
   dim3 tile[3] = {dim3(64, 2), dim3(64, 1), dim3(128, 1)};
+  bool tile_set = false;  // the caller chose a shape: the launches that take shapes are used
   // captured whole steps (one graph per ping-pong parity), replayed by fdcgks_step
   int graph_steps = 16;  // steps per captured graph; 0: separate launches
   bool fuse_nodes = false;  // node sweep inside the update kernel
@@ -2252,12 +2389,9 @@ fdcgks_status launch_check(fdcgks_problem* pb, const char* what) {
 // ---- 2D stage sequence
 fdcgks_status halo2d(fdcgks_problem* pb, double* S) {
   const Geo& g = pb->g;
-  long nr = (long)pb->nplanes * 2 * HALO * (g.nx + g.sx);
-  long nc = (long)pb->nplanes * (g.ny + g.sy + 2 * HALO) * 2 * HALO;
-  hipLaunchKernelGGL(k_halo_rows, dim3(std::min(ceil_div(nr, 256), 4096)), dim3(256), 0, pb->stream, S,
-                     pb->nplanes, g, pb->sc);
-  hipLaunchKernelGGL(k_halo_cols, dim3(std::min(ceil_div(nc, 256), 4096)), dim3(256), 0, pb->stream, S,
-                     pb->nplanes, g, pb->sc);
+  const long n = (long)pb->nplanes * 2 * HALO * (g.nx + g.sx + 2 * HALO + g.ny + g.sy);
+  hipLaunchKernelGGL(k_halo, dim3(std::min(ceil_div(n, 256), 4096)), dim3(256), 0, pb->stream, S, pb->nplanes, g,
+                     pb->sc);
   mark(pb, TK_HALO);
   return launch_check(pb, "halo");
 }
@@ -2299,6 +2433,31 @@ void launch_update(fdcgks_problem* pb, const double* Sin, const double* Ain, dou
                      pb->nparts);
 }
 
+// The joined launches of a stage.
+template <int STAGE>
+void launch_sweeps(fdcgks_problem* pb, const double* Sin) {
+  const Geo& g = pb->g;
+  const dim3 blk(64, 2);
+  const int w = node_reach(pb->k);
+  const int etx = ceil_div(g.nx + 2 + OX, 64), ent = etx * (g.ny + 3 + g.sy);
+  const int ntx = ceil_div(g.nx + w + OX, 64), nnt = ntx * ceil_div(g.ny + 2 * w + g.sy, 2);
+  const int epad = ceil_div(ent, NXCD) * NXCD, npad = ceil_div(nnt, NXCD) * NXCD;
+  const bool f32 = pb->prm.flux_precision == FDCGKS_FP32_FLUX;
+  const bool ch = pb->prm.recon_vars == FDCGKS_RECON_CHARACTERISTIC;
+  auto fn = f32 ? (ch ? k_sweeps2d<STAGE, float, true> : k_sweeps2d<STAGE, float, false>)
+                : (ch ? k_sweeps2d<STAGE, double, true> : k_sweeps2d<STAGE, double, false>);
+  hipLaunchKernelGGL(fn, dim3(2 * epad + 2 * npad), blk, 0, pb->stream, Sin, pb->E, pb->Nb, g, pb->k, pb->sc, etx, ent,
+                     epad, ntx, nnt, npad);
+}
+template <int STAGE>
+void launch_update_comps(fdcgks_problem* pb, const double* Sin, const double* Ain, double* Out, double* Aout) {
+  const Geo& g = pb->g;
+  auto fn = pb->k.flux_order == 8 ? k_update_comps2d<STAGE, true> : k_update_comps2d<STAGE, false>;
+  double* fold = STAGE == 2 && pb->cfl_fold ? pb->part : nullptr;
+  hipLaunchKernelGGL(fn, dim3(ceil_div(g.nx + g.sx, 64), g.ny + g.sy, 2), dim3(64, 4), 0, pb->stream, Sin, pb->E, pb->Nb,
+                     Ain, Out, Aout, g, pb->k, pb->sc, fold, pb->nparts);
+}
+
 // Launch of the fused interface sweep + update (k_fused2d): strips of FS_W
 // node columns, each cut into chunks of rows so that about two blocks per CU
 // run at once.
@@ -2327,7 +2486,9 @@ void launch_fused(fdcgks_problem* pb, const double* Sin, const double* Ain, doub
 // update; 1 the node sweep inside the update kernel; 2 the interface sweep
 // fused with the update after the node sweep.  Both fusions need periodic
 // axes and the order-6 flux; otherwise the separate kernels run.
-enum { STAGE_SEPARATE = 0, STAGE_FUSE_NODES = 1, STAGE_FUSE_IFACE = 2 };
+// 3 the two sweeps in one launch and the per-component update that leaves its
+// output's ghosts filled (any sides and flux order).
+enum { STAGE_SEPARATE = 0, STAGE_FUSE_NODES = 1, STAGE_FUSE_IFACE = 2, STAGE_JOINED = 3 };
 // Whether the fused stage kernel beats the separate sweeps (the automatic
 // choice): its blocks march the rows of one strip of columns in lock step,
 // so it needs tall row chunks at about two blocks per compute unit, here at
@@ -2337,20 +2498,32 @@ bool fused_pays(const fdcgks_problem* pb) {
   const long strips = ceil_div(pb->g.nx, FS_W);
   return (long)pb->g.ny * strips >= 64L * 2 * pb->ncu;
 }
+// Unfused stages join their launches at every size (k_sweeps2d has both sides
+// measured) unless the caller chose launch shapes, which the launches of their
+// own take.
+int unfused_mode(const fdcgks_problem* pb) { return pb->tile_set ? STAGE_SEPARATE : STAGE_JOINED; }
 int stage_mode(const fdcgks_problem* pb) {
-  if ((pb->g.sx | pb->g.sy) || pb->k.flux_order == 8 || pb->prm.dim != 2) return STAGE_SEPARATE;
+  if ((pb->g.sx | pb->g.sy) || pb->k.flux_order == 8 || pb->prm.dim != 2) return unfused_mode(pb);
   if (pb->fuse_stage == 1 || (pb->fuse_stage == 2 && fused_pays(pb))) return STAGE_FUSE_IFACE;
-  return pb->fuse_nodes ? STAGE_FUSE_NODES : STAGE_SEPARATE;
+  return pb->fuse_nodes ? STAGE_FUSE_NODES : unfused_mode(pb);
 }
 
 // One stage in launch mode `mode` (stage_mode; callers that read the
 // interface or node buffers afterwards pass STAGE_SEPARATE).
 template <int STAGE>
 fdcgks_status stage2d(fdcgks_problem* pb, const double* Sin, const double* Ain, double* Out, double* Aout,
-                      int mode) {
+                      int mode, bool ghosts = false) {
   const Geo& g = pb->g;
-  fdcgks_status st = halo2d(pb, const_cast<double*>(Sin));
+  // ghosts: the launch that wrote Sin filled its ghosts
+  fdcgks_status st = ghosts ? FDCGKS_OK : halo2d(pb, const_cast<double*>(Sin));
   if (st) return st;
+  if (mode == STAGE_JOINED) {
+    launch_sweeps<STAGE>(pb, Sin);
+    mark(pb, STAGE == 1 ? TK_EDGE1 : TK_EDGE2);
+    launch_update_comps<STAGE>(pb, Sin, Ain, Out, Aout);
+    mark(pb, STAGE == 1 ? TK_UPD1 : TK_UPD2);
+    return launch_check(pb, "stage");
+  }
   if (mode == STAGE_FUSE_IFACE) {
     launch_nodes<STAGE>(pb, Sin, pb->tile[1]);
     mark(pb, STAGE == 1 ? TK_NODE1 : TK_NODE2);
@@ -2385,7 +2558,8 @@ bool fold_ok(const fdcgks_problem* pb, double dt) {
 
 // fresh: reduce the CFL partials from the state (the first step of a call or
 // graph); otherwise the previous step's stage-2 update folded them.
-fdcgks_status begin_step(fdcgks_problem* pb, double dt, double cfl, bool fresh = true) {
+// advance: the launch also ends the step before.
+fdcgks_status begin_step(fdcgks_problem* pb, double dt, double cfl, bool fresh = true, bool advance = false) {
   const Geo& g = pb->g;
   int use_cfl = dt > 0 ? 0 : 1;
   if (use_cfl && fresh) {
@@ -2398,7 +2572,7 @@ fdcgks_status begin_step(fdcgks_problem* pb, double dt, double cfl, bool fresh =
                          gstride, pb->k.gamma, pb->part, pb->sc);
   }
   hipLaunchKernelGGL(k_step_begin, dim3(1), dim3(256), 0, pb->stream, pb->part, pb->nparts, pb->sc, cfl, g.h,
-                     pb->k.mu, use_cfl);
+                     pb->k.mu, use_cfl, advance ? 1 : 0);
   return launch_check(pb, "step_begin");
 }
 
@@ -2440,6 +2614,20 @@ fdcgks_status launch_run1d(fdcgks_problem* pb, int mode, int nsteps, double dt, 
   return launch_check(pb, "run1d");
 }
 
+// The launches of one 2D step from S[cc], its end (k_step_end) left to the
+// next step's begin.  first: of a call or graph (the time step's partials and
+// the state's ghosts are not there yet).
+fdcgks_status one_step(fdcgks_problem* pb, double dt, double cfl, int cc, bool first) {
+  const int mode = stage_mode(pb);
+  fdcgks_status st = begin_step(pb, dt, cfl, first || !fold_ok(pb, dt), !first);
+  mark(pb, TK_STEP);
+  if (!st) st = stage2d<1>(pb, pb->S[cc], nullptr, pb->Sstar, pb->Acc, mode, mode == STAGE_JOINED && !first);
+  pb->cfl_fold = fold_ok(pb, dt);
+  if (!st) st = stage2d<2>(pb, pb->Sstar, pb->Acc, pb->S[1 - cc], nullptr, mode, mode == STAGE_JOINED);
+  pb->cfl_fold = false;
+  return st;
+}
+
 // ---- captured steps
 void graph_invalidate(fdcgks_problem* pb) {
   for (hipGraphExec_t& x : pb->gx)
@@ -2468,12 +2656,8 @@ fdcgks_status capture_steps(fdcgks_problem* pb, double dt, double cfl) {
     fdcgks_status st = FDCGKS_OK;
     for (int q = 0, cc = c; q < pb->graph_steps && !st; ++q, cc = 1 - cc) {
       pb->cur = cc;
-      st = begin_step(pb, dt, cfl, q == 0 || !fold_ok(pb, dt));
-      if (!st) st = stage2d<1>(pb, pb->S[cc], nullptr, pb->Sstar, pb->Acc, stage_mode(pb));
-      pb->cfl_fold = fold_ok(pb, dt);
-      if (!st) st = stage2d<2>(pb, pb->Sstar, pb->Acc, pb->S[1 - cc], nullptr, stage_mode(pb));
-      pb->cfl_fold = false;
-      if (!st) {
+      st = one_step(pb, dt, cfl, cc, q == 0);
+      if (!st && q == pb->graph_steps - 1) {
         hipLaunchKernelGGL(k_step_end, dim3(1), dim3(1), 0, pb->stream, pb->sc);
         st = launch_check(pb, "step_end");
       }
@@ -2965,18 +3149,15 @@ fdcgks_status fdcgks_step(fdcgks_problem* pb, double dt, double cfl, int32_t nst
     }
     if (st) nsteps = 0;
   }
-  for (int s = 0; s < nsteps; ++s) {
+  for (int s = 0; s < nsteps && !st; ++s) {
     pb->cur = cur;
-    st = begin_step(pb, dt, cfl, s == 0 || !fold_ok(pb, dt));
-    mark(pb, TK_STEP);
-    if (!st) st = stage2d<1>(pb, pb->S[cur], nullptr, pb->Sstar, pb->Acc, stage_mode(pb));
-    pb->cfl_fold = fold_ok(pb, dt);
-    if (!st) st = stage2d<2>(pb, pb->Sstar, pb->Acc, pb->S[1 - cur], nullptr, stage_mode(pb));
-    pb->cfl_fold = false;
-    if (st) break;
+    st = one_step(pb, dt, cfl, cur, s == 0);
+    cur = 1 - cur;
+  }
+  if (!st && nsteps > 0) {
     hipLaunchKernelGGL(k_step_end, dim3(1), dim3(1), 0, pb->stream, pb->sc);
     mark(pb, TK_STEP);
-    cur = 1 - cur;
+    st = launch_check(pb, "step_end");
   }
   fdcgks_status st2 = read_scal(pb);
   if (st) return st;
@@ -3227,10 +3408,11 @@ fdcgks_status fdcgks_step_vjp(fdcgks_problem* pb, double dt, const double* lam_o
   double* scratch = pb->S[1 - pb->cur];
   pb->E = pb->E1;
   pb->Nb = pb->Nb1;
-  if (!st) st = stage2d<1>(pb, pb->S[pb->cur], nullptr, pb->Sstar, pb->Acc, STAGE_SEPARATE);
+  const int mode = unfused_mode(pb);  // the reverse sweeps read the interface and node buffers
+  if (!st) st = stage2d<1>(pb, pb->S[pb->cur], nullptr, pb->Sstar, pb->Acc, mode);
   pb->E = E0;
   pb->Nb = N0;
-  if (!st) st = stage2d<2>(pb, pb->Sstar, pb->Acc, scratch, nullptr, STAGE_SEPARATE);
+  if (!st) st = stage2d<2>(pb, pb->Sstar, pb->Acc, scratch, nullptr, mode, mode == STAGE_JOINED);
   if (!st) st = read_scal(pb);
   if (st) return st;
   if (pb->sc_host->stop & 1)
@@ -3283,6 +3465,7 @@ fdcgks_status fdcgks_set_option(fdcgks_problem* pb, int32_t option, int64_t valu
       if (value < 0 || (value >> 32) != 0 || !tile_ok(c, x, y))
         return fail(pb, FDCGKS_EINVAL, "invalid launch shape %u x %u for kernel class %d", x, y, c);
       pb->tile[c] = dim3(x, y);
+      pb->tile_set = true;
       graph_invalidate(pb);
       return FDCGKS_OK;
     }

@@ -143,3 +143,44 @@ def test_autotune_keeps_results():
     b.step(nsteps=3, cfl=0.5)
     assert np.array_equal(a.get_state_all(), b.get_state_all())
     print("autotuned shapes at 128^2:", tiles)
+
+
+@pytest.mark.parametrize("name", ["reflecting_x_70x37", "reflecting_all_67x9", "no_slip_ns_40x8",
+                                  "zero_gradient_riemann_33", "mixed_48x20", "reflecting_all_char_67x9",
+                                  "periodic_4x4", "periodic_order8_5x4", "bounded_4x5", "periodic_fp32_65x3n"])
+def test_joined_launches_match_separate(name):
+    """The joined launches (sweeps together, a thread per component, ghosts
+    written by the update) against those of their own, which a chosen launch
+    shape selects: bitwise, eager and captured."""
+    from paper_2606_17772_amd import Problem
+    from tests import test_gpu_boundaries as TB
+    if name in TB.CASES:
+        s, P, D = TB.CASES[name]()
+    elif name == "bounded_4x5":
+        nx, ny = 4, 5
+        P, D = WL.sample_bounded(WL.mirror_flow(1.0, ny / nx, 1, 1), nx, ny, 1.0 / nx, 1, 1)
+        s = settings(dim=2, nx=nx, ny=ny, lx=1.0, mu=1e-3,
+                     sides=["reflecting", "zero_gradient", "no_slip", "reflecting"])
+    else:
+        nx, ny, kw = {"periodic_4x4": (4, 4, {}), "periodic_order8_5x4": (5, 4, dict(flux_order=8)),
+                      "periodic_fp32_65x3n": (65, 9, dict(fp32_flux=True))}[name]
+        pr = WL.random_smooth2d(nx, ny, seed=11)
+        s, P, D = settings(dim=2, nx=nx, ny=ny, lx=1.0, **kw), pr.P, pr.D
+
+    def make(separate, **opt):
+        pb = Problem(gpu_params(s))
+        if separate:
+            pb.set_tile("edge", 64, 2)
+        pb.set_state_stacked(0, P)
+        pb.set_state_stacked(1, D)
+        for k, v in opt.items():
+            setattr(pb, k, v)
+        return pb
+
+    a, b, c = make(False, use_graph=False), make(False, graph_steps=2), make(True, use_graph=False)
+    for rep in range(2):
+        got = [pb.step(nsteps=5, cfl=0.4) for pb in (a, b, c)]
+        assert got[0] == got[1] == got[2] and got[0][1] == 5
+        for g in (0, 1):
+            want = c.get_state_stacked(g)
+            assert np.array_equal(a.get_state_stacked(g), want) and np.array_equal(b.get_state_stacked(g), want), (rep, g)
