@@ -301,21 +301,18 @@ __device__ __forceinline__ void line_adjoint(const double* __restrict__ S, doubl
 }
 
 // Reverse of the interface sweep: same thread layout as the forward sweep
-// (two threads per point, partners in neighbouring waves).  The adjoint of a
-// solve runs in phases (see gks_iface_b) whose largest needs about 380
-// registers; the solve's inputs, their adjoint accumulators, the moment
-// adjoints and the time-coefficient adjoints live in LDS (155 KB per block:
-// one block of four waves per CU, one wave per SIMD), so that only a few
-// values spill.
+// (two threads per point, partners in neighbouring waves).  A solve's inputs
+// and the adjoints of its outputs live in LDS (40 slots a thread), so that the
+// registers hold one state's terms at a time (see gks_iface_b): about 445 of
+// them, one wave per SIMD.  Held to 256 (two waves) 226 spill: 4.1 and 2.3
+// against 2.0 and 1.8 ms at 1024^2.
 // The normal along y (fam != G) swaps rho U and rho V in the local frame:
 // the swap is applied to the data, so one copy of the solver adjoint serves
 // both normals.
 template <int STAGE, bool CHAR>
 __global__ __launch_bounds__(256, 1) void k_adj_edges(const double* __restrict__ S, const double* __restrict__ lamE,
                                                       double* __restrict__ lamS, Geo g, Consts k, double dt, Tiles3 tl) {
-  __shared__ double xch[4][4][64];
-  __shared__ fdk::SolveIO s_in[256], s_inb[256];
-  __shared__ fdk::AccB s_ab[256];
+  __shared__ double slots[fdk::IO_SLOTS][256];
   int bx, by, bz;
   if (!xcd_tile3(tl, bx, by, bz)) return;  // block-uniform
   const int fam = bz;
@@ -324,8 +321,10 @@ __global__ __launch_bounds__(256, 1) void k_adj_edges(const double* __restrict__
   const int j = by * 2 + (ty >> 1) + (fam == 0 ? -1 - g.sy : -2);
   const bool valid = i <= (fam == 0 ? g.nx : g.nx + 1) && j <= (fam == 0 ? g.ny + 1 : g.ny);
   const bool swap = fam != G;
-  fdk::SolveIO& in = s_in[tid];
-  fdk::SolveIO& inb = s_inb[tid];
+  const fdk::SolveIO<256> io{&slots[0][tid]};
+  // exchange with the partner thread (the other G) through slots the solve fills later or has done with
+  double(*const xch)[256] = slots + fdk::IO_F;
+  const int mate = tid ^ 64;
   bool chi_right = false;  // chi = min(chi_l, chi_r) of the density line took chi_r (ties: left)
   {
     fdk::IfaceRec rec[4];
@@ -336,19 +335,18 @@ __global__ __launch_bounds__(256, 1) void k_adj_edges(const double* __restrict__
       for (int c = 0; c < 4; ++c) rec[c] = fdk::IfaceRec{1.0, 0.0, 1.0, 1.0, 0.0, 1.0};
     }
 #pragma unroll
-    for (int c = 0; c < 4; ++c) xch[ty][c][tx] = 0.5 * (rec[c].dl + rec[c].dr);
+    for (int c = 0; c < 4; ++c) xch[c][tid] = 0.5 * (rec[c].dl + rec[c].dr);
     __syncthreads();
     // solve inputs in the local frame (global component of local slot c: q0 when swapped)
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       const int q0 = c == 1 ? 2 : (c == 2 ? 1 : c);
       const int q = swap ? q0 : c;
-      in.WL[c] = rec[q].vl;
-      in.WR[c] = rec[q].vr;
-      in.nL[c] = rec[q].dl;
-      in.nR[c] = rec[q].dr;
-      in.Wt[c] = xch[ty ^ 1][q][tx];
-      inb.WL[c] = inb.WR[c] = inb.nL[c] = inb.nR[c] = inb.Wt[c] = 0.0;
+      io(fdk::IO_WL + c) = rec[q].vl;
+      io(fdk::IO_WR + c) = rec[q].vr;
+      io(fdk::IO_NL + c) = rec[q].dl;
+      io(fdk::IO_NR + c) = rec[q].dr;
+      io(fdk::IO_WT + c) = valid ? xch[q][mate] : 0.0;
     }
     chi_right = rec[0].cr < rec[0].cl;
   }
@@ -356,36 +354,34 @@ __global__ __launch_bounds__(256, 1) void k_adj_edges(const double* __restrict__
   double lchi = 0.0;
   if (valid) {
     const long pl = g.plane, o = at(g, j, i);
-    const double* le0 = lamE + ((long)fam * 50 + G * 25) * pl + o;
-    const double* lp0 = lamE + ((long)fam * 50 + (1 - G) * 25) * pl + o;  // partner slot
-    // output adjoints, read inside the solver adjoint's first phase (the
-    // addresses are formed there too: hoisted out of its phase loop they
-    // would hold 32 registers through every phase)
-    auto obload = [&](fdk::GksIO<double, 2>& ob) {
-      const double* le = fdk::opaque_ptr(le0);
-      const double* lp = fdk::opaque_ptr(lp0);
+    const double* le = lamE + ((long)fam * 50 + G * 25) * pl + o;
+    const double* lp = lamE + ((long)fam * 50 + (1 - G) * 25) * pl + o;  // partner slot
+    double wl[4], wr[4];
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        // blend^T: W~(own) = W^/2 + (partner W^l + W^r)/4 and W~(partner) = W^p/2 + (own W^l + W^r)/4
-        const int q0 = c == 1 ? 2 : (c == 2 ? 1 : c);
-        const int q = swap ? q0 : c;
-        const double ps = lp[(9 + q) * pl] + lp[(13 + q) * pl], pst = lp[(17 + q) * pl] + lp[(21 + q) * pl];
-        ob.Ft[c] = le[(4 + q) * pl];
-        ob.Wlt[c] = 0.5 * le[(17 + q) * pl] + 0.25 * pst;
-        ob.Wrt[c] = 0.5 * le[(21 + q) * pl] + 0.25 * pst;
-        ob.F[c] = STAGE == 1 ? le[q * pl] : 0.0;
-        ob.Wl[c] = STAGE == 1 ? 0.5 * le[(9 + q) * pl] + 0.25 * ps : 0.0;
-        ob.Wr[c] = STAGE == 1 ? 0.5 * le[(13 + q) * pl] + 0.25 * ps : 0.0;
+    for (int c = 0; c < 4; ++c) {
+      // blend^T: W~(own) = W^/2 + (partner W^l + W^r)/4 and W~(partner) = W^p/2 + (own W^l + W^r)/4
+      const int q0 = c == 1 ? 2 : (c == 2 ? 1 : c);
+      const int q = swap ? q0 : c;
+      const double pst = lp[(17 + q) * pl] + lp[(21 + q) * pl];
+      io(fdk::IO_FT + c) = le[(4 + q) * pl];
+      io(fdk::IO_WLT + c) = 0.5 * le[(17 + q) * pl] + 0.25 * pst;
+      io(fdk::IO_WRT + c) = 0.5 * le[(21 + q) * pl] + 0.25 * pst;
+      if (STAGE == 1) {
+        const double ps = lp[(9 + q) * pl] + lp[(13 + q) * pl];
+        io(fdk::IO_F + c) = le[q * pl];
+        wl[c] = 0.5 * le[(9 + q) * pl] + 0.25 * ps;
+        wr[c] = 0.5 * le[(13 + q) * pl] + 0.25 * ps;
+        io(fdk::IO_W + c) = wl[c] + wr[c];
       }
-    };
-    lchi = le0[8 * pl];
-    fdk::gks_iface_b(k, dt, in, obload, inb, s_ab[tid]);
+    }
+    lchi = le[8 * pl];
+    fdk::gks_iface_b<STAGE == 1>(k, dt, io, wl, wr);
   }
   // the tangential slope of this solve came from the partner line: send its lambda
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
     const int q0 = c == 1 ? 2 : (c == 2 ? 1 : c);
-    xch[ty][c][tx] = swap && q0 != c ? inb.Wt[q0] : inb.Wt[c];  // global component c
+    xch[c][tid] = io(fdk::IO_WT + (swap ? q0 : c));  // global component c
   }
   __syncthreads();
   if (valid) {
@@ -394,12 +390,12 @@ __global__ __launch_bounds__(256, 1) void k_adj_edges(const double* __restrict__
     for (int c = 0; c < 4; ++c) {
       const int q0 = c == 1 ? 2 : (c == 2 ? 1 : c);
       const int q = swap ? q0 : c;  // local slot of global component c
-      const double lt = 0.5 * xch[ty ^ 1][c][tx];  // partner's tangential slope = mean of my dl, dr
-      lv[c][0] = inb.WL[q];
-      lv[c][1] = inb.nL[q] + lt;
+      const double lt = 0.5 * xch[c][mate];  // partner's tangential slope = mean of my dl, dr
+      lv[c][0] = io(fdk::IO_WL + q);
+      lv[c][1] = io(fdk::IO_NL + q) + lt;
       lv[c][2] = 0.0;
-      lv[c][3] = inb.WR[q];
-      lv[c][4] = inb.nR[q] + lt;
+      lv[c][3] = io(fdk::IO_WR + q);
+      lv[c][4] = io(fdk::IO_NR + q) + lt;
       lv[c][5] = 0.0;
     }
     if (!CHAR) {
@@ -443,16 +439,14 @@ __global__ __launch_bounds__(256) void k_adj_nodes(const double* __restrict__ S,
     node_derivs<CHAR, double>(B, g, k, o, Wx, Wy);
     double lF[4], lFt[4], lG[4], lGt[4];
     for (int c = 0; c < 4; ++c) {
-      lF[c] = ln[c * pl];
+      lF[c] = STAGE == 1 ? ln[c * pl] : 0.0;
       lFt[c] = ln[(4 + c) * pl];
-      lG[c] = ln[(8 + c) * pl];
+      lG[c] = STAGE == 1 ? ln[(8 + c) * pl] : 0.0;
       lGt[c] = ln[(12 + c) * pl];
     }
     // nodal solver^T (stage 2 has no F, G outputs)
     double Wb[4] = {0, 0, 0, 0}, Wxb[4] = {0, 0, 0, 0}, Wyb[4] = {0, 0, 0, 0};
-    if (STAGE == 2)
-      for (int c = 0; c < 4; ++c) { lF[c] = 0.0; lG[c] = 0.0; }
-    fdk::gks_node_b(k, W, Wx, Wy, lF, lFt, lG, lGt, Wb, Wxb, Wyb);
+    fdk::gks_node_b<STAGE == 1>(k, W, Wx, Wy, lF, lFt, lG, lGt, Wb, Wxb, Wyb);
 #pragma unroll
     for (int c = 0; c < 4; ++c) own[c][t] += Wb[c];
     // the 3-point line of axis a, component q: adjoints of W (qb) and of the axis's derivative plane (xb) at
