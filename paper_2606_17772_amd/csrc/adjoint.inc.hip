@@ -236,83 +236,124 @@ __global__ __launch_bounds__(256) void k_adj_nodeflux(const double* __restrict__
 }
 
 // ------------------------------------------------------- solver^T, GENO^T
+// A line's 4 nodes of W and of the derivative plane along it, for the four
+// components, into slots of LDS (a thread's slots 256 doubles apart): the sweep
+// reads them early, with its other loads, and GENO^T finds them there.
+enum { LINE_W = fdk::IO_SLOTS, LINE_X = LINE_W + 16, ADJ_SLOTS = LINE_X + 16 };
+__device__ __forceinline__ long line_origin(const Geo& g, int i, int j, int fam, int G) {
+  const int back = G == 0 ? 1 : 2;
+  return (fam != G ? at(g, j - back, i) : at(g, j, i - back)) + (G ? g.dshift : 0);  // shifted dual planes
+}
+__device__ __forceinline__ void load_line(const double* __restrict__ S, const Geo& g, int i, int j, int fam, int G,
+                                          const fdk::SolveIO<256>& io) {
+  const bool ALONG_Y = fam != G;
+  const long st = ALONG_Y ? g.pitch : 1, o = line_origin(g, i, j, fam, G), pl = g.plane;
+  const int f = ALONG_Y ? 2 : 1;
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      io(LINE_W + 4 * c + m) = S[(G * 12 + c) * pl + o + m * st];
+      io(LINE_X + 4 * c + m) = S[(G * 12 + f * 4 + c) * pl + o + m * st];
+    }
+}
+
+// v[m] goes to l[m * st].  Along x (st = 1) the lanes' lines overlap: each lane
+// takes what it and the three lanes before it have for its first node (one
+// atomic instead of four); what the last three lanes have for the nodes beyond
+// comes round to the first three, which add it 64 nodes on.
+__device__ __forceinline__ void add_line(double* l, long st, bool along_x, bool valid, const double (&v)[4]) {
+  if (!along_x) {
+    if (valid)
+#pragma unroll
+      for (int m = 0; m < 4; ++m)
+        if (v[m] != 0.0) atomicAdd(l + m * st, v[m]);
+    return;
+  }
+  const int tx = threadIdx.x & 63;
+  double in = valid ? v[0] : 0.0, out = 0.0;
+#pragma unroll
+  for (int m = 1; m < 4; ++m) {
+    const double t = __shfl(valid ? v[m] : 0.0, (tx - m) & 63);
+    if (tx >= m) in += t;
+    else out += t;
+  }
+  if (in != 0.0) atomicAdd(l, in);
+  if (out != 0.0) atomicAdd(l + 64, out);
+}
+
 // GENO^T of one line: lam of (vl, dl, cl, vr, dr, cr) per component ->
 // scatter onto the line's nodes (W plane and derivative plane).  fam and G
 // are runtime values (wave-uniform): one copy of the code serves all lines.
+// Every lane of the wave comes here; those without a point (valid = false)
+// only pass on what the others have for their nodes.
 // CHAR: the line was reconstructed on characteristic variables in its local
 // frame (edge_recon<true>); lv's cl, cr entries are unused and chib is the
 // adjoint of the line's single path function.
 template <bool CHAR>
-__device__ __forceinline__ void line_adjoint(const double* __restrict__ S, double* __restrict__ lamS, const Geo& g,
-                                             const Consts& k, int i, int j, int fam, int G,
+__device__ __forceinline__ void line_adjoint(double* __restrict__ lamS, const Geo& g, const Consts& k, int i, int j,
+                                             int fam, int G, bool valid, const fdk::SolveIO<256>& io,
                                              const double (&lv)[4][6], double chib) {
   const bool ALONG_Y = (fam ^ G) != 0;
-  const int back = G == 0 ? 1 : 2;
-  const long st = ALONG_Y ? g.pitch : 1;
-  const long o = (ALONG_Y ? at(g, j - back, i) : at(g, j, i - back)) + (G ? g.dshift : 0);  // shifted dual planes
+  const long st = ALONG_Y ? g.pitch : 1, o = line_origin(g, i, j, fam, G), pl = g.plane;
   const int f = ALONG_Y ? 2 : 1;
-  const long pl = g.plane;
   if constexpr (CHAR) {
     // local component c holds global component q (rho U and rho V trade places along y), as in edge_recon
     double Q[4][4], X[4][4], rb[4][4], Qb[4][4], Xb[4][4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-      const int q = ALONG_Y ? (c == 1 ? 2 : (c == 2 ? 1 : c)) : c;
-      const double* w = S + (G * 12 + q) * pl + o;
-      const double* x = S + (G * 12 + f * 4 + q) * pl + o;
+      const int q0 = c == 1 ? 2 : (c == 2 ? 1 : c), q = ALONG_Y ? q0 : c;
 #pragma unroll
       for (int m = 0; m < 4; ++m) {
-        Q[c][m] = w[m * st];
-        X[c][m] = x[m * st];
+        Q[c][m] = io(LINE_W + 4 * q + m);
+        X[c][m] = io(LINE_X + 4 * q + m);
         Qb[c][m] = Xb[c][m] = 0.0;
       }
-      rb[c][0] = lv[q][0];
-      rb[c][1] = lv[q][1];
-      rb[c][2] = lv[q][3];
-      rb[c][3] = lv[q][4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int u = t < 2 ? t : t + 1;
+        rb[c][t] = ALONG_Y ? lv[q0][u] : lv[c][u];
+      }
     }
-    fdk::recon_iface_char_b(k, Q, X, g.h, g.invh, rb, chib, Qb, Xb);
+    if (valid) fdk::recon_iface_char_b(k, Q, X, g.h, g.invh, rb, chib, Qb, Xb);
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-      const int q = ALONG_Y ? (c == 1 ? 2 : (c == 2 ? 1 : c)) : c;
-      double* lw = lamS + (G * 12 + q) * pl + o;
-      double* lx = lamS + (G * 12 + f * 4 + q) * pl + o;
-      for (int m = 0; m < 4; ++m) {
-        if (Qb[c][m] != 0.0) atomicAdd(lw + m * st, Qb[c][m]);
-        if (Xb[c][m] != 0.0) atomicAdd(lx + m * st, Xb[c][m]);
-      }
+      const int q0 = c == 1 ? 2 : (c == 2 ? 1 : c), q = ALONG_Y ? q0 : c;
+      add_line(lamS + (G * 12 + q) * pl + o, st, !ALONG_Y, valid, Qb[c]);
+      add_line(lamS + (G * 12 + f * 4 + q) * pl + o, st, !ALONG_Y, valid, Xb[c]);
     }
     return;
   }
+#pragma unroll
   for (int c = 0; c < 4; ++c) {
-    const double* w = S + (G * 12 + c) * pl + o;
-    const double* x = S + (G * 12 + f * 4 + c) * pl + o;
-    const double q[4] = {w[0], w[st], w[2 * st], w[3 * st]};
-    const double xv[4] = {x[0], x[st], x[2 * st], x[3 * st]};
-    double qb[4] = {0, 0, 0, 0}, xb[4] = {0, 0, 0, 0};
-    fdk::recon_iface_b(k, q, xv, g.h, g.invh, lv[c], qb, xb);
-    double* lw = lamS + (G * 12 + c) * pl + o;
-    double* lx = lamS + (G * 12 + f * 4 + c) * pl + o;
+    double q[4], xv[4], qb[4] = {0, 0, 0, 0}, xb[4] = {0, 0, 0, 0};
+#pragma unroll
     for (int m = 0; m < 4; ++m) {
-      if (qb[m] != 0.0) atomicAdd(lw + m * st, qb[m]);
-      if (xb[m] != 0.0) atomicAdd(lx + m * st, xb[m]);
+      q[m] = io(LINE_W + 4 * c + m);
+      xv[m] = io(LINE_X + 4 * c + m);
     }
+    if (valid) fdk::recon_iface_b(k, q, xv, g.h, g.invh, lv[c], qb, xb);
+    add_line(lamS + (G * 12 + c) * pl + o, st, !ALONG_Y, valid, qb);
+    add_line(lamS + (G * 12 + f * 4 + c) * pl + o, st, !ALONG_Y, valid, xb);
   }
 }
 
 // Reverse of the interface sweep: same thread layout as the forward sweep
 // (two threads per point, partners in neighbouring waves).  A solve's inputs
-// and the adjoints of its outputs live in LDS (40 slots a thread), so that the
+// and the adjoints of its outputs live in LDS, with its line's values (72 slots a
+// thread and the partners' exchange, 152 KB per block of four waves), so that the
 // registers hold one state's terms at a time (see gks_iface_b): about 445 of
 // them, one wave per SIMD.  Held to 256 (two waves) 226 spill: 4.1 and 2.3
-// against 2.0 and 1.8 ms at 1024^2.
+// against 2.0 and 1.8 ms at 1024^2.  With one wave every wait counts: all loads
+// at the start, smooth lines' GENO^T as the linear map it is, and a quarter of
+// the atomics for lines along x make it 1.69 and 1.47 ms.
 // The normal along y (fam != G) swaps rho U and rho V in the local frame:
 // the swap is applied to the data, so one copy of the solver adjoint serves
 // both normals.
 template <int STAGE, bool CHAR>
 __global__ __launch_bounds__(256, 1) void k_adj_edges(const double* __restrict__ S, const double* __restrict__ lamE,
                                                       double* __restrict__ lamS, Geo g, Consts k, double dt, Tiles3 tl) {
-  __shared__ double slots[fdk::IO_SLOTS][256];
+  __shared__ double slots[ADJ_SLOTS][256], xch[4][256];
   int bx, by, bz;
   if (!xcd_tile3(tl, bx, by, bz)) return;  // block-uniform
   const int fam = bz;
@@ -322,9 +363,33 @@ __global__ __launch_bounds__(256, 1) void k_adj_edges(const double* __restrict__
   const bool valid = i <= (fam == 0 ? g.nx : g.nx + 1) && j <= (fam == 0 ? g.ny + 1 : g.ny);
   const bool swap = fam != G;
   const fdk::SolveIO<256> io{&slots[0][tid]};
-  // exchange with the partner thread (the other G) through slots the solve fills later or has done with
-  double(*const xch)[256] = slots + fdk::IO_F;
   const int mate = tid ^ 64;
+  // every load of the sweep at the start: the adjoints of the outputs, then the line
+  double wl[4], wr[4], lchi = 0.0;
+  if (valid) {
+    const long pl = g.plane, o = at(g, j, i);
+    const double* le = lamE + ((long)fam * 50 + G * 25) * pl + o;
+    const double* lp = lamE + ((long)fam * 50 + (1 - G) * 25) * pl + o;  // partner slot
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      // blend^T: W~(own) = W^/2 + (partner W^l + W^r)/4 and W~(partner) = W^p/2 + (own W^l + W^r)/4
+      const int q0 = c == 1 ? 2 : (c == 2 ? 1 : c);
+      const int q = swap ? q0 : c;
+      const double pst = lp[(17 + q) * pl] + lp[(21 + q) * pl];
+      io(fdk::IO_FT + c) = le[(4 + q) * pl];
+      io(fdk::IO_WLT + c) = 0.5 * le[(17 + q) * pl] + 0.25 * pst;
+      io(fdk::IO_WRT + c) = 0.5 * le[(21 + q) * pl] + 0.25 * pst;
+      if (STAGE == 1) {
+        const double ps = lp[(9 + q) * pl] + lp[(13 + q) * pl];
+        io(fdk::IO_F + c) = le[q * pl];
+        wl[c] = 0.5 * le[(9 + q) * pl] + 0.25 * ps;
+        wr[c] = 0.5 * le[(13 + q) * pl] + 0.25 * ps;
+        io(fdk::IO_W + c) = wl[c] + wr[c];
+      }
+    }
+    lchi = le[8 * pl];
+    load_line(S, g, i, j, fam, G, io);
+  }
   bool chi_right = false;  // chi = min(chi_l, chi_r) of the density line took chi_r (ties: left)
   {
     fdk::IfaceRec rec[4];
@@ -351,30 +416,7 @@ __global__ __launch_bounds__(256, 1) void k_adj_edges(const double* __restrict__
     chi_right = rec[0].cr < rec[0].cl;
   }
   __syncthreads();
-  double lchi = 0.0;
   if (valid) {
-    const long pl = g.plane, o = at(g, j, i);
-    const double* le = lamE + ((long)fam * 50 + G * 25) * pl + o;
-    const double* lp = lamE + ((long)fam * 50 + (1 - G) * 25) * pl + o;  // partner slot
-    double wl[4], wr[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      // blend^T: W~(own) = W^/2 + (partner W^l + W^r)/4 and W~(partner) = W^p/2 + (own W^l + W^r)/4
-      const int q0 = c == 1 ? 2 : (c == 2 ? 1 : c);
-      const int q = swap ? q0 : c;
-      const double pst = lp[(17 + q) * pl] + lp[(21 + q) * pl];
-      io(fdk::IO_FT + c) = le[(4 + q) * pl];
-      io(fdk::IO_WLT + c) = 0.5 * le[(17 + q) * pl] + 0.25 * pst;
-      io(fdk::IO_WRT + c) = 0.5 * le[(21 + q) * pl] + 0.25 * pst;
-      if (STAGE == 1) {
-        const double ps = lp[(9 + q) * pl] + lp[(13 + q) * pl];
-        io(fdk::IO_F + c) = le[q * pl];
-        wl[c] = 0.5 * le[(9 + q) * pl] + 0.25 * ps;
-        wr[c] = 0.5 * le[(13 + q) * pl] + 0.25 * ps;
-        io(fdk::IO_W + c) = wl[c] + wr[c];
-      }
-    }
-    lchi = le[8 * pl];
     fdk::gks_iface_b<STAGE == 1>(k, dt, io, wl, wr);
   }
   // the tangential slope of this solve came from the partner line: send its lambda
@@ -384,25 +426,23 @@ __global__ __launch_bounds__(256, 1) void k_adj_edges(const double* __restrict__
     xch[c][tid] = io(fdk::IO_WT + (swap ? q0 : c));  // global component c
   }
   __syncthreads();
-  if (valid) {
-    double lv[4][6];
+  double lv[4][6];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int q0 = c == 1 ? 2 : (c == 2 ? 1 : c);
-      const int q = swap ? q0 : c;  // local slot of global component c
-      const double lt = 0.5 * xch[c][mate];  // partner's tangential slope = mean of my dl, dr
-      lv[c][0] = io(fdk::IO_WL + q);
-      lv[c][1] = io(fdk::IO_NL + q) + lt;
-      lv[c][2] = 0.0;
-      lv[c][3] = io(fdk::IO_WR + q);
-      lv[c][4] = io(fdk::IO_NR + q) + lt;
-      lv[c][5] = 0.0;
-    }
-    if (!CHAR) {
-      if (chi_right) lv[0][5] = lchi; else lv[0][2] = lchi;
-    }
-    line_adjoint<CHAR>(S, lamS, g, k, i, j, fam, G, lv, CHAR ? lchi : 0.0);
+  for (int c = 0; c < 4; ++c) {
+    const int q0 = c == 1 ? 2 : (c == 2 ? 1 : c);
+    const int q = swap ? q0 : c;  // local slot of global component c
+    const double lt = 0.5 * xch[c][mate];  // partner's tangential slope = mean of my dl, dr
+    lv[c][0] = io(fdk::IO_WL + q);
+    lv[c][1] = io(fdk::IO_NL + q) + lt;
+    lv[c][2] = 0.0;
+    lv[c][3] = io(fdk::IO_WR + q);
+    lv[c][4] = io(fdk::IO_NR + q) + lt;
+    lv[c][5] = 0.0;
   }
+  if (!CHAR) {
+    if (chi_right) lv[0][5] = lchi; else lv[0][2] = lchi;
+  }
+  line_adjoint<CHAR>(lamS, g, k, i, j, fam, G, valid, io, lv, CHAR ? lchi : 0.0);
 }
 
 // Reverse of the node sweep: lambda of the nodal fluxes -> lambda of the

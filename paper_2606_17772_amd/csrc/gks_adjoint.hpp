@@ -284,7 +284,8 @@ template <int STRIDE> struct SolveIO {
 // the states.  A last part takes tau and W0 back to the two sides.
 // Against the reverse of the moment vectors of psi (seven phases, half of them
 // recomputing a side's state) the reverse interface sweep at 1024^2 takes 2.01
-// and 1.83 (stage 2) instead of 3.4 ms, the node sweep 0.58 instead of 1.05.
+// and 1.83 (stage 2) instead of 3.4 ms, the node sweep 0.58 instead of 1.05
+// (0.48 since smooth lines skip GENO's reverse).
 template <bool VALUES, int STRIDE>
 FDK_HD void gks_iface_b(const Consts& k, double dt, const SolveIO<STRIDE>& io, const double* wl, const double* wr) {
   const double K = k.K, gam = k.gamma, g1 = gam - 1.0, kappa = 0.5 * (K + 1.0), hK = 0.5 * (K + 2.0);
@@ -692,63 +693,72 @@ FDK_HD void recon_iface_b(const Consts& k, const double q[4], const double x[4],
     const double hx0 = h * x[0], hx3 = h * x[3];
     const double s2 = q0 - 2.0 * q1 + q2, s3 = q1 - 2.0 * q2 + q3;
     const double D2 = s2 * s2, D3 = s3 * s3;
-    const double dmid = (q2 - q1) * invh;
-    const double qc = (-q0 + 6.0 * q1 + 3.0 * q2) * 0.125;
-    const double PHl = ((7.0 * q0 + 35.0 * q1 + 21.0 * q2 + q3) + (x[0] + 22.0 * x[1] - 7.0 * x[2]) * h) * (1.0 / 64.0);
-    const double PHr = ((q0 + 21.0 * q1 + 35.0 * q2 + 7.0 * q3) + (7.0 * x[1] - 22.0 * x[2] - x[3]) * h) * (1.0 / 64.0);
-    const double PHx = -((q0 + 45.0 * q1 - 45.0 * q2 - q3) + 9.0 * (x[1] + x[2]) * h) * (invh * (1.0 / 30.0));
     const double Al = q1 - q0 - hx0, Bl = 2.0 * (q1 - q0) - hx0, El = 3.0 * q1 - 4.0 * q2 + q3;
     const double Ar = q2 - q3 + hx3, Br = 2.0 * (q3 - q2) - hx3, Er = 3.0 * q2 - 4.0 * q1 + q0;
-    GenoIn L{(13.0 / 3.0) * Al * Al + Bl * Bl, (13.0 / 12.0) * D2 + 0.25 * sqr(q2 - q0),
-             (13.0 / 12.0) * D3 + 0.25 * El * El, (-5.0 * q0 + 9.0 * q1 - 3.0 * hx0) * 0.25, qc,
-             (3.0 * q1 + 6.0 * q2 - q3) * 0.125, (-3.0 * q0 + 3.0 * q1 - 2.0 * hx0) * invh, dmid, dmid, PHl, PHx};
-    GenoIn R{(13.0 / 3.0) * Ar * Ar + Br * Br, (13.0 / 12.0) * D3 + 0.25 * sqr(q3 - q1),
-             (13.0 / 12.0) * D2 + 0.25 * Er * Er, (-5.0 * q3 + 9.0 * q2 + 3.0 * hx3) * 0.25,
-             (-q3 + 6.0 * q2 + 3.0 * q1) * 0.125, qc, (-3.0 * q2 + 3.0 * q3 - 2.0 * hx3) * invh, dmid, dmid, PHr, PHx};
-    GenoIn Lb{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0}, Rb{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-    geno_b(k, L, k.ds, k.dc, k.ds, rb[0], rb[1], rb[2], Lb);
-    geno_b(k, R, k.ds, k.dc, k.ds, rb[3], rb[4], rb[5], Rb);
-    PHlb = Lb.PH;
-    PHrb = Rb.PH;
-    PHxb = Lb.PHx + Rb.PHx;
-    double hx0b = 0.0, hx3b = 0.0, D2b = 0.0, D3b = 0.0;
-    const double qcb = Lb.q2 + Rb.q3, dmidb = Lb.dq2 + Lb.dq3 + Rb.dq2 + Rb.dq3;
-    // right side
-    qb[2] += -3.0 * invh * Rb.dq1; qb[3] += 3.0 * invh * Rb.dq1; hx3b += -2.0 * invh * Rb.dq1;
-    qb[3] += -0.125 * Rb.q2; qb[2] += 0.75 * Rb.q2; qb[1] += 0.375 * Rb.q2;
-    qb[3] += -1.25 * Rb.q1; qb[2] += 2.25 * Rb.q1; hx3b += 0.75 * Rb.q1;
-    {
-      D2b += (13.0 / 12.0) * Rb.IS3;
-      const double Eb = 0.5 * Er * Rb.IS3;
-      qb[2] += 3.0 * Eb; qb[1] += -4.0 * Eb; qb[0] += Eb;
-      D3b += (13.0 / 12.0) * Rb.IS2;
-      const double t = 0.5 * (q3 - q1) * Rb.IS2;
-      qb[3] += t; qb[1] -= t;
-      const double Ab = (26.0 / 3.0) * Ar * Rb.IS1, Bb = 2.0 * Br * Rb.IS1;
-      qb[2] += Ab - 2.0 * Bb; qb[3] += -Ab + 2.0 * Bb; hx3b += Ab - Bb;
+    const double ISl1 = (13.0 / 3.0) * Al * Al + Bl * Bl, ISl2 = (13.0 / 12.0) * D2 + 0.25 * sqr(q2 - q0),
+                 ISl3 = (13.0 / 12.0) * D3 + 0.25 * El * El;
+    const double ISr1 = (13.0 / 3.0) * Ar * Ar + Br * Br, ISr2 = (13.0 / 12.0) * D3 + 0.25 * sqr(q3 - q1),
+                 ISr3 = (13.0 / 12.0) * D2 + 0.25 * Er * Er;
+    // smooth lines (chi = 1 on both sides, see geno_smooth) are linear in their values
+    if ((int)geno_smooth<double>(k, ISl1, ISl2, ISl3) & (int)geno_smooth<double>(k, ISr1, ISr2, ISr3)) {
+      PHlb = rb[0];
+      PHrb = rb[3];
+      PHxb = rb[1] + rb[4];
+    } else {
+      const double dmid = (q2 - q1) * invh;
+      const double qc = (-q0 + 6.0 * q1 + 3.0 * q2) * 0.125;
+      const double PHl = ((7.0 * q0 + 35.0 * q1 + 21.0 * q2 + q3) + (x[0] + 22.0 * x[1] - 7.0 * x[2]) * h) * (1.0 / 64.0);
+      const double PHr = ((q0 + 21.0 * q1 + 35.0 * q2 + 7.0 * q3) + (7.0 * x[1] - 22.0 * x[2] - x[3]) * h) * (1.0 / 64.0);
+      const double PHx = -((q0 + 45.0 * q1 - 45.0 * q2 - q3) + 9.0 * (x[1] + x[2]) * h) * (invh * (1.0 / 30.0));
+      GenoIn L{ISl1, ISl2, ISl3, (-5.0 * q0 + 9.0 * q1 - 3.0 * hx0) * 0.25, qc,
+               (3.0 * q1 + 6.0 * q2 - q3) * 0.125, (-3.0 * q0 + 3.0 * q1 - 2.0 * hx0) * invh, dmid, dmid, PHl, PHx};
+      GenoIn R{ISr1, ISr2, ISr3, (-5.0 * q3 + 9.0 * q2 + 3.0 * hx3) * 0.25,
+               (-q3 + 6.0 * q2 + 3.0 * q1) * 0.125, qc, (-3.0 * q2 + 3.0 * q3 - 2.0 * hx3) * invh, dmid, dmid, PHr, PHx};
+      GenoIn Lb{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0}, Rb{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+      geno_b(k, L, k.ds, k.dc, k.ds, rb[0], rb[1], rb[2], Lb);
+      geno_b(k, R, k.ds, k.dc, k.ds, rb[3], rb[4], rb[5], Rb);
+      PHlb = Lb.PH;
+      PHrb = Rb.PH;
+      PHxb = Lb.PHx + Rb.PHx;
+      double hx0b = 0.0, hx3b = 0.0, D2b = 0.0, D3b = 0.0;
+      const double qcb = Lb.q2 + Rb.q3, dmidb = Lb.dq2 + Lb.dq3 + Rb.dq2 + Rb.dq3;
+      // right side
+      qb[2] += -3.0 * invh * Rb.dq1; qb[3] += 3.0 * invh * Rb.dq1; hx3b += -2.0 * invh * Rb.dq1;
+      qb[3] += -0.125 * Rb.q2; qb[2] += 0.75 * Rb.q2; qb[1] += 0.375 * Rb.q2;
+      qb[3] += -1.25 * Rb.q1; qb[2] += 2.25 * Rb.q1; hx3b += 0.75 * Rb.q1;
+      {
+        D2b += (13.0 / 12.0) * Rb.IS3;
+        const double Eb = 0.5 * Er * Rb.IS3;
+        qb[2] += 3.0 * Eb; qb[1] += -4.0 * Eb; qb[0] += Eb;
+        D3b += (13.0 / 12.0) * Rb.IS2;
+        const double t = 0.5 * (q3 - q1) * Rb.IS2;
+        qb[3] += t; qb[1] -= t;
+        const double Ab = (26.0 / 3.0) * Ar * Rb.IS1, Bb = 2.0 * Br * Rb.IS1;
+        qb[2] += Ab - 2.0 * Bb; qb[3] += -Ab + 2.0 * Bb; hx3b += Ab - Bb;
+      }
+      // left side
+      qb[0] += -3.0 * invh * Lb.dq1; qb[1] += 3.0 * invh * Lb.dq1; hx0b += -2.0 * invh * Lb.dq1;
+      qb[1] += 0.375 * Lb.q3; qb[2] += 0.75 * Lb.q3; qb[3] += -0.125 * Lb.q3;
+      qb[0] += -1.25 * Lb.q1; qb[1] += 2.25 * Lb.q1; hx0b += -0.75 * Lb.q1;
+      {
+        D3b += (13.0 / 12.0) * Lb.IS3;
+        const double Eb = 0.5 * El * Lb.IS3;
+        qb[1] += 3.0 * Eb; qb[2] += -4.0 * Eb; qb[3] += Eb;
+        D2b += (13.0 / 12.0) * Lb.IS2;
+        const double t = 0.5 * (q2 - q0) * Lb.IS2;
+        qb[2] += t; qb[0] -= t;
+        const double Ab = (26.0 / 3.0) * Al * Lb.IS1, Bb = 2.0 * Bl * Lb.IS1;
+        qb[1] += Ab + 2.0 * Bb; qb[0] += -Ab - 2.0 * Bb; hx0b += -Ab - Bb;
+      }
+      // shared
+      qb[0] += -0.125 * qcb; qb[1] += 0.75 * qcb; qb[2] += 0.375 * qcb;
+      qb[2] += invh * dmidb; qb[1] -= invh * dmidb;
+      const double s3b = 2.0 * s3 * D3b, s2b = 2.0 * s2 * D2b;
+      qb[1] += s3b; qb[2] += -2.0 * s3b; qb[3] += s3b;
+      qb[0] += s2b; qb[1] += -2.0 * s2b; qb[2] += s2b;
+      xb[0] += h * hx0b;
+      xb[3] += h * hx3b;
     }
-    // left side
-    qb[0] += -3.0 * invh * Lb.dq1; qb[1] += 3.0 * invh * Lb.dq1; hx0b += -2.0 * invh * Lb.dq1;
-    qb[1] += 0.375 * Lb.q3; qb[2] += 0.75 * Lb.q3; qb[3] += -0.125 * Lb.q3;
-    qb[0] += -1.25 * Lb.q1; qb[1] += 2.25 * Lb.q1; hx0b += -0.75 * Lb.q1;
-    {
-      D3b += (13.0 / 12.0) * Lb.IS3;
-      const double Eb = 0.5 * El * Lb.IS3;
-      qb[1] += 3.0 * Eb; qb[2] += -4.0 * Eb; qb[3] += Eb;
-      D2b += (13.0 / 12.0) * Lb.IS2;
-      const double t = 0.5 * (q2 - q0) * Lb.IS2;
-      qb[2] += t; qb[0] -= t;
-      const double Ab = (26.0 / 3.0) * Al * Lb.IS1, Bb = 2.0 * Bl * Lb.IS1;
-      qb[1] += Ab + 2.0 * Bb; qb[0] += -Ab - 2.0 * Bb; hx0b += -Ab - Bb;
-    }
-    // shared
-    qb[0] += -0.125 * qcb; qb[1] += 0.75 * qcb; qb[2] += 0.375 * qcb;
-    qb[2] += invh * dmidb; qb[1] -= invh * dmidb;
-    const double s3b = 2.0 * s3 * D3b, s2b = 2.0 * s2 * D2b;
-    qb[1] += s3b; qb[2] += -2.0 * s3b; qb[3] += s3b;
-    qb[0] += s2b; qb[1] += -2.0 * s2b; qb[2] += s2b;
-    xb[0] += h * hx0b;
-    xb[3] += h * hx3b;
   }
   const double c = 1.0 / 64.0, kx = -invh * (1.0 / 30.0);
   qb[0] += 7.0 * c * PHlb + c * PHrb + kx * PHxb;
@@ -769,34 +779,36 @@ FDK_HD void recon_node_b(const Consts& k, const double q[3], const double x[3], 
   if (k.variant != 2) {
     const double q0 = q[0], q1 = q[1], q2 = q[2];
     const double hx0 = h * x[0], hx2 = h * x[2];
-    const double PHx = (9.0 * (q0 - q2) + h * (x[0] + 46.0 * x[1] + x[2])) * (invh * (1.0 / 30.0));
     const double A1 = q1 - q0 - hx0, B1 = 2.0 * (q1 - q0) - hx0;
     const double A2 = q2 - q1 - hx2, B2 = 2.0 * (q2 - q1) - hx2;
     const double s = q0 - 2.0 * q1 + q2, u = q2 - q0;
     const double IS1 = (13.0 / 3.0) * A1 * A1 + B1 * B1;
     const double IS2 = (13.0 / 3.0) * A2 * A2 + B2 * B2;
     const double IS3 = (13.0 / 12.0) * s * s + 0.25 * u * u;
-    GenoIn g{IS3, IS1, IS2, q1, q1, q1, (q2 - q0) * (0.5 * invh), (-2.0 * q0 + 2.0 * q1 - hx0) * invh,
-             (-2.0 * q1 + 2.0 * q2 - hx2) * invh, q1, PHx};
-    GenoIn gb{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-    geno_b(k, g, k.dc, k.ds, k.ds, 0.0, db, 0.0, gb);
-    PHxb = gb.PHx;
-    double hx0b = 0.0, hx2b = 0.0;
-    qb[1] += gb.q1 + gb.q2 + gb.q3 + gb.PH;
-    qb[2] += 0.5 * invh * gb.dq1;
-    qb[0] -= 0.5 * invh * gb.dq1;
-    qb[0] += -2.0 * invh * gb.dq2; qb[1] += 2.0 * invh * gb.dq2; hx0b += -invh * gb.dq2;
-    qb[1] += -2.0 * invh * gb.dq3; qb[2] += 2.0 * invh * gb.dq3; hx2b += -invh * gb.dq3;
-    {
-      const double sb = (13.0 / 6.0) * s * gb.IS1, ub = 0.5 * u * gb.IS1;
-      qb[0] += sb - ub; qb[1] += -2.0 * sb; qb[2] += sb + ub;
-      const double Ab2 = (26.0 / 3.0) * A2 * gb.IS3, Bb2 = 2.0 * B2 * gb.IS3;
-      qb[2] += Ab2 + 2.0 * Bb2; qb[1] += -Ab2 - 2.0 * Bb2; hx2b += -Ab2 - Bb2;
-      const double Ab1 = (26.0 / 3.0) * A1 * gb.IS2, Bb1 = 2.0 * B1 * gb.IS2;
-      qb[1] += Ab1 + 2.0 * Bb1; qb[0] += -Ab1 - 2.0 * Bb1; hx0b += -Ab1 - Bb1;
+    if (!geno_smooth<double>(k, IS3, IS1, IS2)) {  // smooth lines are linear in their values: PHxb = db
+      const double PHx = (9.0 * (q0 - q2) + h * (x[0] + 46.0 * x[1] + x[2])) * (invh * (1.0 / 30.0));
+      GenoIn g{IS3, IS1, IS2, q1, q1, q1, (q2 - q0) * (0.5 * invh), (-2.0 * q0 + 2.0 * q1 - hx0) * invh,
+               (-2.0 * q1 + 2.0 * q2 - hx2) * invh, q1, PHx};
+      GenoIn gb{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+      geno_b(k, g, k.dc, k.ds, k.ds, 0.0, db, 0.0, gb);
+      PHxb = gb.PHx;
+      double hx0b = 0.0, hx2b = 0.0;
+      qb[1] += gb.q1 + gb.q2 + gb.q3 + gb.PH;
+      qb[2] += 0.5 * invh * gb.dq1;
+      qb[0] -= 0.5 * invh * gb.dq1;
+      qb[0] += -2.0 * invh * gb.dq2; qb[1] += 2.0 * invh * gb.dq2; hx0b += -invh * gb.dq2;
+      qb[1] += -2.0 * invh * gb.dq3; qb[2] += 2.0 * invh * gb.dq3; hx2b += -invh * gb.dq3;
+      {
+        const double sb = (13.0 / 6.0) * s * gb.IS1, ub = 0.5 * u * gb.IS1;
+        qb[0] += sb - ub; qb[1] += -2.0 * sb; qb[2] += sb + ub;
+        const double Ab2 = (26.0 / 3.0) * A2 * gb.IS3, Bb2 = 2.0 * B2 * gb.IS3;
+        qb[2] += Ab2 + 2.0 * Bb2; qb[1] += -Ab2 - 2.0 * Bb2; hx2b += -Ab2 - Bb2;
+        const double Ab1 = (26.0 / 3.0) * A1 * gb.IS2, Bb1 = 2.0 * B1 * gb.IS2;
+        qb[1] += Ab1 + 2.0 * Bb1; qb[0] += -Ab1 - 2.0 * Bb1; hx0b += -Ab1 - Bb1;
+      }
+      xb[0] += h * hx0b;
+      xb[2] += h * hx2b;
     }
-    xb[0] += h * hx0b;
-    xb[2] += h * hx2b;
   }
   const double kx = invh * (1.0 / 30.0);
   qb[0] += 9.0 * kx * PHxb;
