@@ -813,20 +813,23 @@ __global__ __launch_bounds__(128, FDCGKS_EDGE_WAVES) void k_sweeps2d(const doubl
   }
 }
 
+// 64 nodes of one row (stored index row of grid `grid`), from column 64 bx: a
+// thread (64 x 4) per node and component.  Every thread of the block must call
+// this; the first wave returns the nodes' wave speeds and densities (want_cfl).
 template <int STAGE, bool WIDE>
-__global__ __launch_bounds__(256) void k_update_comps2d(const double* __restrict__ S, const double* __restrict__ E,
-                                                        const double* __restrict__ Nb, const double* __restrict__ Ain,
-                                                        double* __restrict__ Out, double* __restrict__ Aout, Geo g, Consts k,
-                                                        Scal* __restrict__ sc, double* __restrict__ part, int nparts) {
-  if (sc->stop) return;  // grid-uniform
+__device__ __forceinline__ void update_comps_row(const double* __restrict__ S, const double* __restrict__ E,
+                                                 const double* __restrict__ Nb, const double* __restrict__ Ain,
+                                                 double* __restrict__ Out, double* __restrict__ Aout, const Geo& g,
+                                                 const Consts& k, double dt, int bx, int row, int grid, Scal* sc, int member,
+                                                 bool want_cfl, double& cfl_s, double& cfl_r) {
   __shared__ double sW[4][64];
-  const int grid = blockIdx.z, c = threadIdx.y, tx = threadIdx.x;
-  const int i = blockIdx.x * 64 + tx - (grid ? g.sx : 0), j = blockIdx.y - (grid ? g.sy : 0);
+  const int c = threadIdx.y, tx = threadIdx.x;
+  const int i = bx * 64 + tx - (grid ? g.sx : 0), j = row - (grid ? g.sy : 0);
   const bool mine = i < g.nx && j < g.ny;
   if (mine) {
     const NodeFluxGlobal nf{Nb + (long)grid * 16 * g.plane + at(g, j, i), g.plane, g.pitch};
     NewNode v;
-    update_comps<STAGE, NodeFluxGlobal, WIDE>(S, E, nf, Ain, Out, Aout, g, k, sc->dt, i, j, grid, c, c + 1, v);
+    update_comps<STAGE, NodeFluxGlobal, WIDE>(S, E, nf, Ain, Out, Aout, g, k, dt, i, j, grid, c, c + 1, v);
     sW[c][tx] = v.W;
     // ghosts, in stored node coordinates
     const int si = i + (grid ? g.sx : 0), sj = j + (grid ? g.sy : 0);
@@ -836,31 +839,39 @@ __global__ __launch_bounds__(256) void k_update_comps2d(const double* __restrict
       for (int f = 0; f < 3; ++f) {
         const double val = f == 0 ? v.W : (f == 1 ? v.GX : v.GY);
         double* P = Out + (long)(grid * 12 + f * 4 + c) * g.plane;
-        auto row = [&](int gj, double vy, bool real) {  // row gj holds vy at column si
+        auto put = [&](int gj, double vy, bool real) {  // row gj holds vy at column si
           if (!real) P[at(g, gj, si)] = vy;
           for_images(si, mx, g.side[0], g.side[1], grid && g.sx, f == 1, c == 1, c == 1 || c == 2,
                      [&](int gi, double fx) { P[at(g, gj, gi)] = fx * vy; });
         };
-        row(sj, val, true);
+        put(sj, val, true);
         for_images(sj, my, g.side[2], g.side[3], grid && g.sy, f == 2, c == 2, c == 1 || c == 2,
-                   [&](int gj, double fy) { row(gj, fy * val, false); });
+                   [&](int gj, double fy) { put(gj, fy * val, false); });
       }
     }
   }
   __syncthreads();
-  if (c != 0) return;
+  if (c != 0 || !mine) return;
+  NewNode v;
+  v.rho = sW[0][tx];
+  v.mU = sW[1][tx];
+  v.mV = sW[2][tx];
+  v.ener = sW[3][tx];
+  v.mom2 = v.mom2 + v.mU * v.mU;
+  v.mom2 = v.mom2 + v.mV * v.mV;
+  update_check<STAGE>(v, k, i, j, grid, sc, member, want_cfl, cfl_s, cfl_r);
+}
+template <int STAGE, bool WIDE>
+__global__ __launch_bounds__(256) void k_update_comps2d(const double* __restrict__ S, const double* __restrict__ E,
+                                                        const double* __restrict__ Nb, const double* __restrict__ Ain,
+                                                        double* __restrict__ Out, double* __restrict__ Aout, Geo g, Consts k,
+                                                        Scal* __restrict__ sc, double* __restrict__ part, int nparts) {
+  if (sc->stop) return;  // grid-uniform
   double cfl_s = 0.0, cfl_r = 1e300;
-  if (mine) {
-    NewNode v;
-    v.rho = sW[0][tx];
-    v.mU = sW[1][tx];
-    v.mV = sW[2][tx];
-    v.ener = sW[3][tx];
-    v.mom2 = v.mom2 + v.mU * v.mU;
-    v.mom2 = v.mom2 + v.mV * v.mV;
-    update_check<STAGE>(v, k, i, j, grid, sc, 0, STAGE == 2 && part, cfl_s, cfl_r);
-  }
-  if (STAGE == 2 && part) cfl_fold(part, nparts, cfl_s, cfl_r);
+  const bool fold = STAGE == 2 && part != nullptr;
+  update_comps_row<STAGE, WIDE>(S, E, Nb, Ain, Out, Aout, g, k, sc->dt, blockIdx.x, blockIdx.y, blockIdx.z, sc, 0, fold,
+                                cfl_s, cfl_r);
+  if (fold && threadIdx.y == 0) cfl_fold(part, nparts, cfl_s, cfl_r);
 }
 
 // ------------------------------------ interface sweep fused with the update
@@ -1970,8 +1981,10 @@ __device__ __forceinline__ double member_dt(const BArgs& a, int m, const Consts&
   return dt;
 }
 
-// CFL partial of one member over stored rows [16 by, 16 by + 16) of both
-// grids (the dual grid has one more row and column along a bounded axis).
+// CFL partial of one member over CFL_ROWS stored rows of both grids (the dual
+// grid has one more row and column along a bounded axis).  16 members of 64^2
+// to 384^2 fill the chip with strips of 4 rows (25 us with the ghosts of a first state; 16 rows: 63 us).
+constexpr int CFL_ROWS = 4;
 __device__ __forceinline__ void cfl_block(const BArgs& a, const Consts& k, const BItem& it, double* red) {
   const BMember& M = a.mem[it.m];
   const Geo& g = M.g;
@@ -1979,7 +1992,7 @@ __device__ __forceinline__ void cfl_block(const BArgs& a, const Consts& k, const
   const int nthr = blockDim.x * blockDim.y, tid = threadIdx.y * blockDim.x + threadIdx.x;
   double vmax = 0.0, rmin = 1e300;
   const int H = g.ny + g.sy, W = g.nx + g.sx;
-  const int j0 = it.by * 16, j1 = min(H, j0 + 16);
+  const int j0 = it.by * CFL_ROWS, j1 = min(H, j0 + CFL_ROWS);
   for (int q = tid; q < 2 * (j1 - j0) * W; q += nthr) {
     int i = q % W, r = q / W, j = j0 + r % (j1 - j0), gr = r / (j1 - j0);
     if (gr == 0 && (i >= g.nx || j >= g.ny)) continue;
@@ -2124,24 +2137,24 @@ __global__ __launch_bounds__(256, 2) void k_batch_stage(BArgs a, Consts k) {
 }
 
 // ---- the same stage as separate launches, one per phase (grid = work items)
-template <int STAGE>
-__global__ __launch_bounds__(256) void k_bphase_halo(BArgs a, Consts k) {
+// The time-step partials, and the ghosts of a first state (items n_cfl onwards;
+// later states and every stage-1 result get theirs from the update).
+__global__ __launch_bounds__(256) void k_bphase_begin(BArgs a, Consts k) {
   if (a.sc->stop) return;
   __shared__ double red[512];
   const int q = blockIdx.x;
-  if (STAGE == 1 && q == 0)
+  if (q == 0)
     for (int m = threadIdx.y * blockDim.x + threadIdx.x; m < a.count; m += blockDim.x * blockDim.y) {
       unsigned long long* nx = a.slots + (long)(a.parity ^ 1) * 2 * a.count;
       nx[m] = 0ull;
       nx[a.count + m] = (unsigned long long)__double_as_longlong(1e300);
     }
-  if (STAGE == 1 && q < a.n_cfl) {
+  if (q < a.n_cfl) {
     cfl_block(a, k, a.items[q], red);
     return;
   }
-  const BItem& it = a.items[a.n_cfl + q - (STAGE == 1 ? a.n_cfl : 0)];
-  const BMember& M = a.mem[it.m];
-  halo_plane_block(STAGE == 1 ? M.S[a.cur] : M.Sstar, M.g, it.z);
+  const BItem& it = a.items[q];
+  halo_plane_block(a.mem[it.m].S[a.cur], a.mem[it.m].g, it.z);
 }
 // CHAR: characteristic reconstruction; WIDE: the order-8 flux (node reach 2).
 template <int STAGE, class FT, bool CHAR>
@@ -2159,19 +2172,21 @@ __global__ __launch_bounds__(256) void k_bphase_nodes(BArgs a, Consts k) {
   const BMember& M = a.mem[w.m];
   node_block<STAGE, FT, CHAR>(STAGE == 1 ? M.S[a.cur] : M.Sstar, M.Nb, M.g, k, w.bx, w.by, w.z, node_reach(k), -OX);
 }
+// Four blocks per item, one for each of its rows.
 template <int STAGE, bool WIDE>
 __global__ __launch_bounds__(256) void k_bphase_update(BArgs a, Consts k) {
   if (a.sc->stop) return;
-  const BItem& w = a.items[a.n_cfl + a.n_halo + a.n_edge + a.n_node + blockIdx.x];
+  const BItem& w = a.items[a.n_cfl + a.n_halo + a.n_edge + a.n_node + (blockIdx.x >> 2)];
   const BMember& M = a.mem[w.m];
   const double dt = member_dt(a, w.m, k);
+  const int row = 4 * w.by + (blockIdx.x & 3);
   double cs = 0.0, cr = 0.0;  // batches reduce their time steps themselves
   if (STAGE == 1)
-    update_block<1, WIDE>(M.S[a.cur], M.E, M.Nb, nullptr, M.Sstar, M.Acc, M.g, k, dt, w.bx, w.by, w.z, a.sc, w.m,
-                          false, cs, cr);
+    update_comps_row<1, WIDE>(M.S[a.cur], M.E, M.Nb, nullptr, M.Sstar, M.Acc, M.g, k, dt, w.bx, row, w.z, a.sc, w.m,
+                              false, cs, cr);
   else
-    update_block<2, WIDE>(M.Sstar, M.E, M.Nb, M.Acc, M.S[a.cur ^ 1], nullptr, M.g, k, dt, w.bx, w.by, w.z, a.sc,
-                          w.m, false, cs, cr);
+    update_comps_row<2, WIDE>(M.Sstar, M.E, M.Nb, M.Acc, M.S[a.cur ^ 1], nullptr, M.g, k, dt, w.bx, row, w.z, a.sc,
+                              w.m, false, cs, cr);
 }
 __global__ void k_bphase_end(BArgs a, Consts k) { batch_step_end(a, k); }
 
@@ -3627,27 +3642,27 @@ bool same_scheme(const fdcgks_params& a, const fdcgks_params& b) {
 constexpr int BATCH_GRAPH_STEPS = 16;
 
 // One batched step as one launch per phase on `stream`.
+// first: of a call or graph (the state's ghosts are not there yet)
 template <class FT, bool CHAR, bool WIDE>
-void batch_phased_step_t(const BArgs& a, const Consts& k, hipStream_t stream) {
+void batch_phased_step_t(const BArgs& a, const Consts& k, hipStream_t stream, bool first) {
   const dim3 blk(64, 4);
-  hipLaunchKernelGGL(k_bphase_halo<1>, dim3(a.n_cfl + a.n_halo), blk, 0, stream, a, k);
+  hipLaunchKernelGGL(k_bphase_begin, dim3(a.n_cfl + (first ? a.n_halo : 0)), blk, 0, stream, a, k);
   hipLaunchKernelGGL((k_bphase_edges<1, FT, CHAR>), dim3(a.n_edge), blk, 0, stream, a, k);
   hipLaunchKernelGGL((k_bphase_nodes<1, FT, CHAR>), dim3(a.n_node), blk, 0, stream, a, k);
-  hipLaunchKernelGGL((k_bphase_update<1, WIDE>), dim3(a.n_upd), blk, 0, stream, a, k);
-  hipLaunchKernelGGL(k_bphase_halo<2>, dim3(a.n_halo), blk, 0, stream, a, k);
+  hipLaunchKernelGGL((k_bphase_update<1, WIDE>), dim3(4 * a.n_upd), blk, 0, stream, a, k);
   hipLaunchKernelGGL((k_bphase_edges<2, FT, CHAR>), dim3(a.n_edge), blk, 0, stream, a, k);
   hipLaunchKernelGGL((k_bphase_nodes<2, FT, CHAR>), dim3(a.n_node), blk, 0, stream, a, k);
-  hipLaunchKernelGGL((k_bphase_update<2, WIDE>), dim3(a.n_upd), blk, 0, stream, a, k);
+  hipLaunchKernelGGL((k_bphase_update<2, WIDE>), dim3(4 * a.n_upd), blk, 0, stream, a, k);
   hipLaunchKernelGGL(k_bphase_end, dim3(1), blk, 0, stream, a, k);
 }
-void batch_phased_step(const BArgs& a, const Consts& k, bool fp32, bool chr, hipStream_t stream) {
-  using Step = void (*)(const BArgs&, const Consts&, hipStream_t);
+void batch_phased_step(const BArgs& a, const Consts& k, bool fp32, bool chr, hipStream_t stream, bool first) {
+  using Step = void (*)(const BArgs&, const Consts&, hipStream_t, bool);
   static const Step steps[2][2][2] = {
       {{batch_phased_step_t<double, false, false>, batch_phased_step_t<double, false, true>},
        {batch_phased_step_t<double, true, false>, batch_phased_step_t<double, true, true>}},
       {{batch_phased_step_t<float, false, false>, batch_phased_step_t<float, false, true>},
        {batch_phased_step_t<float, true, false>, batch_phased_step_t<float, true, true>}}};
-  steps[fp32][chr][k.flux_order == 8](a, k, stream);
+  steps[fp32][chr][k.flux_order == 8](a, k, stream, first);
 }
 
 // The cooperative persistent kernel of one stage for the batch's scheme.
@@ -3739,7 +3754,7 @@ fdcgks_status fdcgks_batch_create(int32_t count, const fdcgks_params* params, vo
     b->mem[m].Nb = alloc((size_t)32 * g.plane * sizeof(double));
     // ranges of the single-problem launches; a bounded axis adds the dual
     // grid's boundary row / column
-    for (int by = 0; by < ceil_div(g.ny + g.sy, 16); ++by) cfl.push_back({m, 0, 0, by});
+    for (int by = 0; by < ceil_div(g.ny + g.sy, CFL_ROWS); ++by) cfl.push_back({m, 0, 0, by});
     for (int pl = 0; pl < 24; ++pl) halo.push_back({m, pl, 0, 0});
     for (int z = 0; z < 2; ++z)
       for (int by = 0; by < ceil_div(g.ny + 3 + g.sy, 2); ++by)
@@ -3903,7 +3918,7 @@ fdcgks_status fdcgks_batch_step(fdcgks_batch* b, double cfl, int32_t nsteps, dou
       for (int q = 0; q < BATCH_GRAPH_STEPS; ++q) {
         a.cur = cur0 ^ (q & 1);
         a.parity = par0 ^ (q & 1);
-        batch_phased_step(a, b->k, fp32, chr, b->cap);
+        batch_phased_step(a, b->k, fp32, chr, b->cap, q == 0);
       }
       hipGraph_t gr = nullptr;
       hipError_t e = hipStreamEndCapture(b->cap, &gr);
@@ -3930,7 +3945,7 @@ fdcgks_status fdcgks_batch_step(fdcgks_batch* b, double cfl, int32_t nsteps, dou
       }
       continue;
     }
-    batch_phased_step(a, b->k, fp32, chr, b->stream);
+    batch_phased_step(a, b->k, fp32, chr, b->stream, s == 0);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return bfail(b, FDCGKS_EHIP, "batched launch failed: %s", hipGetErrorString(e));
   }
