@@ -225,8 +225,19 @@ class Problem:
         ps, dev, _ = _ptr(S)
         self._chk(self._L.fdcgks_set_state_from_samples(self._h, ps, dev))
 
+    def _get_state_into(self, grid, out):
+        """Grid `grid` into a contiguous host array (3 or 2 times ncomp, ...): the
+        fields' addresses lie in it, so that nothing is joined afterwards."""
+        n = self.ncomp
+        py = C.c_void_p(out[2 * n:].ctypes.data) if self.params.dim == 2 else C.c_void_p(None)
+        self._chk(self._L.fdcgks_get_state(self._h, grid, C.c_void_p(out.ctypes.data), C.c_void_p(out[n:].ctypes.data),
+                                           py, 0, 0))
+
     def get_state_stacked(self, grid):
-        return np.concatenate(self.get_state(grid), axis=0)
+        shape = self.grid_shape(grid)
+        out = np.empty(((3 if self.params.dim == 2 else 2) * shape[0],) + tuple(shape[1:]))
+        self._get_state_into(grid, out)
+        return out
 
     def set_state_all(self, S):
         """S: (ngrid, 12, ny, nx) (2D) stacked W, Wx, Wy of every grid, as a
@@ -245,9 +256,13 @@ class Problem:
         """(ngrid, 3*ncomp, ny, nx) as numpy (device=None) or a torch tensor on `device`."""
         if any(self.bounded):
             raise ValueError("grids differ in size along bounded axes: use get_state per grid")
-        parts = [self.get_state(g, device) for g in range(self.ngrid)]
         if device is None:
-            return np.stack([np.concatenate(p, axis=0) for p in parts])
+            shape = self.grid_shape(0)
+            out = np.empty((self.ngrid, (3 if self.params.dim == 2 else 2) * shape[0]) + tuple(shape[1:]))
+            for g in range(self.ngrid):
+                self._get_state_into(g, out[g])
+            return out
+        parts = [self.get_state(g, device) for g in range(self.ngrid)]
         torch = _torch()
         return torch.stack([torch.cat(p, dim=0) for p in parts])
 
@@ -475,9 +490,10 @@ class Batch:
                        np.ascontiguousarray(S[8:12]))
 
     def get_state_stacked(self, member, grid):
-        out = [np.empty((4,) + self.grid_dims(member, grid)) for _ in range(3)]
-        self._chk(self._L.fdcgks_batch_get_state(self._h, member, grid, *(C.c_void_p(a.ctypes.data) for a in out), 0))
-        return np.concatenate(out, axis=0)
+        out = np.empty((12,) + self.grid_dims(member, grid))
+        self._chk(self._L.fdcgks_batch_get_state(self._h, member, grid,
+                                                 *(C.c_void_p(out[q:].ctypes.data) for q in (0, 4, 8)), 0))
+        return out
 
     def set_mode(self, mode):
         """'graph' (one launch per phase, 16 steps per captured HIP graph;
