@@ -449,23 +449,32 @@ __global__ __launch_bounds__(256, 1) void k_adj_edges(const double* __restrict__
 // node's W and of the 3-point lines its derivative reconstructions read.
 // Block 64 x 4 nodes, one wave per row.  A node's reverse adds to 12 planes
 // of itself and to 8 planes of each neighbour along x and y (W and that
-// axis's derivative plane).  Each thread parks its contributions in LDS
-// slots of its own as they are produced; after a barrier every node sums
-// what it received from the adjacent lanes and rows of the block and adds
-// the 12 sums atomically (neighbouring blocks add to the same nodes), and
-// only contributions that leave the block go out one by one.
+// axis's derivative plane).  Each thread keeps those to its own node in
+// registers and parks the others in LDS slots of its own as they are produced
+// (64 KB a block: two blocks per CU, where slots for its own node too left
+// room for one: 0.87 -> 0.55 ms at 1024^2; the characteristic form needs its
+// registers and has one wave per SIMD anyway, so it parks them all).  After a
+// barrier every node sums what it received from the adjacent lanes and rows of
+// the block and adds the 12 sums atomically (neighbouring blocks add to the
+// same nodes), and only contributions that leave the block go out one by one.
 template <int STAGE, bool CHAR>
-__global__ __launch_bounds__(256) void k_adj_nodes(const double* __restrict__ S, const double* __restrict__ lamN,
+__global__ __launch_bounds__(256, CHAR ? 1 : 2) void k_adj_nodes(const double* __restrict__ S, const double* __restrict__ lamN,
                                                    double* __restrict__ lamS, Geo g, Consts k, Tiles3 tl) {
-  // [slot][thread]: own[p] = plane p of this node; to_xm / to_xp / to_ym / to_yp [s] = the node at i -/+ 1 or
+  // own(p): plane p of this node.  [slot][thread]: to_xm / to_xp / to_ym / to_yp [s] = the node at i -/+ 1 or
   // j -/+ 1, plane s for s < 4 (W), else the axis's derivative plane (4 + s along x, 8 + (s - 4) along y)
-  __shared__ double own[12][256], to_xm[8][256], to_xp[8][256], to_ym[8][256], to_yp[8][256];
+  __shared__ double own_lds[CHAR ? 12 : 1][256], to_xm[8][256], to_xp[8][256], to_ym[8][256], to_yp[8][256];
   int bx, by, bz;
   if (!xcd_tile3(tl, bx, by, bz)) return;  // block-uniform
   const int grid = bz, w = node_reach(k), tx = threadIdx.x, ty = threadIdx.y, t = ty * 64 + tx;
   const int i = bx * 64 + tx - w - (grid ? g.sx : 0);
   const int j = by * 4 + ty - w - (grid ? g.sy : 0);
-  for (int p = 0; p < 12; ++p) own[p][t] = 0.0;
+  double own_reg[12];
+  auto own = [&](int p) -> double& {
+    if constexpr (CHAR) return own_lds[p][t];
+    else return own_reg[p];
+  };
+#pragma unroll
+  for (int p = 0; p < 12; ++p) own(p) = 0.0;
   for (int s8 = 0; s8 < 8; ++s8) { to_xm[s8][t] = 0.0; to_xp[s8][t] = 0.0; to_ym[s8][t] = 0.0; to_yp[s8][t] = 0.0; }
   const long pl = g.plane, o = at(g, j, i);
   const long ds = grid ? g.dshift : 0;  // state planes: shifted dual
@@ -488,12 +497,12 @@ __global__ __launch_bounds__(256) void k_adj_nodes(const double* __restrict__ S,
     double Wb[4] = {0, 0, 0, 0}, Wxb[4] = {0, 0, 0, 0}, Wyb[4] = {0, 0, 0, 0};
     fdk::gks_node_b<STAGE == 1>(k, W, Wx, Wy, lF, lFt, lG, lGt, Wb, Wxb, Wyb);
 #pragma unroll
-    for (int c = 0; c < 4; ++c) own[c][t] += Wb[c];
+    for (int c = 0; c < 4; ++c) own(c) += Wb[c];
     // the 3-point line of axis a, component q: adjoints of W (qb) and of the axis's derivative plane (xb) at
     // offsets -1, 0, +1
     auto park = [&](int a, int q, const double* qb, const double* xb) {
-      own[q][t] += qb[1];
-      own[(a + 1) * 4 + q][t] += xb[1];
+      own(q) += qb[1];
+      own((a + 1) * 4 + q) += xb[1];
       if (a == 0) {
         to_xm[q][t] = qb[0]; to_xm[4 + q][t] = xb[0]; to_xp[q][t] = qb[2]; to_xp[4 + q][t] = xb[2];
       } else {
@@ -555,8 +564,9 @@ __global__ __launch_bounds__(256) void k_adj_nodes(const double* __restrict__ S,
   }
   // this node's sums (nodes beyond the computed range hold what a computed neighbour handed over, or nothing)
   if (i > g.nx + w || j > g.ny + w) return;
+#pragma unroll
   for (int p = 0; p < 12; ++p) {
-    double v = own[p][t];
+    double v = own(p);
     if (p < 8) {
       if (tx > 0) v += to_xp[p][t - 1];
       if (tx < 63) v += to_xm[p][t + 1];
