@@ -270,7 +270,9 @@ fdcgks_status fdcgks_debug_intermediates(fdcgks_problem* pb, double dt, double* 
  * 64 x 2 (interface), 64 x 1 (node), 128 x 1 (update), the autotuner's pick
  * on a 2048^2 Navier-Stokes problem.
  * The shape changes only the launch, never the arithmetic: results are
- * bitwise identical for every valid shape.
+ * bitwise identical for every valid shape.  Unfused stages run their two
+ * sweeps in one launch of fixed shape and update by component; setting any of
+ * the three selects a launch per kernel, with the shapes set.
  * FDCGKS_OPT_FUSE_NODES (default 0): 1 makes 2D steps evaluate the nodal fluxes
  * inside the update kernel (per 64 x 4 tile plus a one-node halo, in LDS)
  * instead of a separate node sweep through a node buffer; the node and
@@ -286,12 +288,12 @@ fdcgks_status fdcgks_debug_intermediates(fdcgks_problem* pb, double dt, double* 
  * interface buffer).  0 runs the separate interface sweep and update
  * through the interface buffer (the interface and update launch shapes then
  * apply).  2 chooses the fused kernel where its row chunks are tall, i.e.
- * ny * ceil(nx / 61) >= 128 * (compute units): 2048^2 and up on MI355X.
+ * ny * ceil(nx / 61) >= 40 * (compute units): about 780^2 and up on MI355X.
  * Bitwise the same results.  Periodic problems with flux_order 6 (the others
  * always take the separate sweeps); it takes precedence over
  * FDCGKS_OPT_FUSE_NODES.
  * FDCGKS_OPT_FUSED_ROWS (default 0): node rows per block of that kernel;
- * 0 chooses about two blocks per compute unit.
+ * 0 chooses about two blocks per compute unit (three at stage 2).
  * EINVAL for an unknown option or an invalid value. */
 enum {
   FDCGKS_OPT_GRAPH = 0,
@@ -307,7 +309,8 @@ fdcgks_status fdcgks_get_option(const fdcgks_problem* pb, int32_t option, int64_
 
 /* Autotuner: times every valid candidate block shape of the three stage-1
  * kernels (reps launches each, HIP events on the problem's stream) on the
- * current state at its CFL 0.4 time step and keeps the fastest per kernel.
+ * current state at its CFL 0.4 time step and keeps the fastest per kernel
+ * (they apply where a launch per kernel runs, see FDCGKS_OPT_TILE_EDGE).
  * The state is not advanced (the stage scratch buffers are overwritten).
  * Synchronises the stream.  1D problems: nothing to tune, returns OK. */
 fdcgks_status fdcgks_autotune(fdcgks_problem* pb, int32_t reps);

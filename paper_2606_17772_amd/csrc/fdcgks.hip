@@ -2504,14 +2504,16 @@ void launch_fused(fdcgks_problem* pb, const double* Sin, const double* Ain, doub
 // 3 the two sweeps in one launch and the per-component update that leaves its
 // output's ghosts filled (any sides and flux order).
 enum { STAGE_SEPARATE = 0, STAGE_FUSE_NODES = 1, STAGE_FUSE_IFACE = 2, STAGE_JOINED = 3 };
-// Whether the fused stage kernel beats the separate sweeps (the automatic
-// choice): its blocks march the rows of one strip of columns in lock step,
-// so it needs tall row chunks at about two blocks per compute unit, here at
-// least 64 rows each.  Measured: 2048^2 5.42 against 5.92 ms per step; 512^2
-// 0.72 against 0.52 ms (16-row chunks).
+// Whether the fused stage kernel beats the unfused stage (the automatic
+// choice): its blocks march the rows of one strip of columns in lock step, so
+// it needs tall row chunks, here 20 rows each at two blocks per compute unit.
+// Per step, fused against unfused, by strips x rows per compute unit: 18
+// (512^2) 436 against 324 us, 33 (700^2) 567 against 587, 36 598 against 603,
+// 63 (1400x700) 932 against 1097, 68 (1024^2) 977 against 1156, 126 (1400^2)
+// 1785 against 2265.
 bool fused_pays(const fdcgks_problem* pb) {
   const long strips = ceil_div(pb->g.nx, FS_W);
-  return (long)pb->g.ny * strips >= 64L * 2 * pb->ncu;
+  return (long)pb->g.ny * strips >= 40L * pb->ncu;
 }
 // Unfused stages join their launches at every size (k_sweeps2d has both sides
 // measured) unless the caller chose launch shapes, which the launches of their
