@@ -40,16 +40,20 @@ HBM_BYTES_PER_NODE_STAGE = 288  # algorithmic: stage 1 reads 12 / writes 24 doub
 # instructions; FETCH_SIZE x 2.000 + WRITE_SIZE x 1.000 after the copy-kernel
 # calibration).  Both are None whenever the kernel has changed since the
 # counters were taken.
-FLOPS_PER_NODE_FUSED_STAGE1 = 6344
-TRAFFIC_BYTES_PER_LAUNCH_FUSED_STAGE1 = 4.981e9
+FLOPS_PER_NODE_FUSED_STAGE1 = 4415
+TRAFFIC_BYTES_PER_LAUNCH_FUSED_STAGE1 = 5.068e9
 # With --separate: the stage-1 interface sweep k_edges2d<1,double,false>, unit
 # one interface point, 2 (n+3)^2 per launch (profiles/k_edges2d_shear2048.md,
-# same counters).
+# same counters).  FLOPS_PER_IFACE_POINT_STAGE1 counts the solver from moment
+# vectors of psi (the source-level operation count runs that form); the FP64
+# kernel, in primitive slopes, executes FLOPS_EXECUTED_PER_IFACE_POINT_STAGE1,
+# which its achieved rate is reckoned from.
 FLOPS_PER_IFACE_POINT_STAGE1 = 5618
+FLOPS_EXECUTED_PER_IFACE_POINT_STAGE1 = 3789
 TRAFFIC_BYTES_PER_LAUNCH_STAGE1 = 4.473e9
 # 3D leg: the stage-1 interface sweep k_edges3d<true,false>, unit one solve
 # (12 per cell), from profiles/k_edges3d_taylor_green128.md (same counters).
-FLOPS_PER_SOLVE_3D_STAGE1 = 4797
+FLOPS_PER_SOLVE_3D_STAGE1 = 2843
 
 
 # Launch shapes fdcgks_autotune picks on this workload (interface sweep,
@@ -736,7 +740,7 @@ def main():
         kernel = "k_fused2d<1,double,false> (stage-1 interface sweep fused with the update)"
     else:
         launch_ms = kms["edge1"] / kn
-        flops_per_unit, units, traffic = FLOPS_PER_IFACE_POINT_STAGE1, 2 * (n + 3) * (n + 3), \
+        flops_per_unit, units, traffic = FLOPS_EXECUTED_PER_IFACE_POINT_STAGE1, 2 * (n + 3) * (n + 3), \
             TRAFFIC_BYTES_PER_LAUNCH_STAGE1
         kernel = "k_edges2d<1,double,false> (stage-1 interface sweep)"
     if flops_per_unit:
