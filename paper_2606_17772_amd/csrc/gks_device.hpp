@@ -991,9 +991,10 @@ FDK_HD void gks_iface_moments(const Consts& k, FT dt, GksIO<FT, DIM>& io) {
 //   <a.psi v'> = V_x,     <a.psi e'> = kappa (theta a(u) + theta_x),  kappa = (K + dim - 1) / 2,
 // so a solve needs 1D moment sums of cubics only.  Bound by FP64 issue and by
 // the registers that set the number of waves: against the moment vectors of
-// psi the stage-1 interface sweep executes 4,541 instead of 5,618 flop per
-// point and holds 180 instead of 246 VGPRs, stage 2 132 instead of 246 (three
-// waves per SIMD): 1.54 and 1.14 ms against 1.55 and 1.40 ms at 2048^2.
+// psi (with GENO's smooth lines decided from one ratio) the stage-1 interface
+// sweep executes 3,789 instead of 5,618 flop per point and holds 180 instead of
+// 246 VGPRs, stage 2 140 instead of 246 (three waves per SIMD): 1.25 and 0.81
+// ms against 1.55 and 1.40 ms at 2048^2.
 template <class FT> struct PSlope {
   FT r, u, v, th;  // rho_x / rho, U_x, V_x, theta_x
 };
