@@ -68,6 +68,18 @@ struct Scal {
 
 __device__ __forceinline__ int imod(int a, int m) { return ((a % m) + m) % m; }
 
+// Whether the run has stopped, one answer for the whole block: the update
+// kernels set the flag themselves, so two waves of a block that starts while
+// another one of the same launch finds a bad node may read it differently, and
+// a wave that left would not have written its share of what the others read
+// after the next barrier.
+__device__ __forceinline__ bool block_stopped(const Scal* __restrict__ sc) {
+  __shared__ int stop;
+  if (threadIdx.x == 0 && threadIdx.y == 0) stop = sc->stop;
+  __syncthreads();
+  return stop != 0;
+}
+
 // XCD-aware tile order.  The GPU deals consecutive workgroup ids round robin
 // to its 8 XCDs, each with its own L2, so row-major tiles put vertically
 // neighbouring tiles (which read the same stencil rows) on different L2s.
@@ -716,7 +728,7 @@ template <int STAGE, class FT, bool CHAR>
 __global__ __launch_bounds__(256) void k_nodeupd2d(const double* __restrict__ S, const double* __restrict__ E,
                                                    const double* __restrict__ Ain, double* __restrict__ Out,
                                                    double* __restrict__ Aout, Geo g, Consts k, Scal* __restrict__ sc) {
-  if (sc->stop) return;  // grid-uniform
+  if (block_stopped(sc)) return;
   __shared__ double xs[8 * 4 * FT_X];
   __shared__ double ys[8 * FT_Y * 64];
   const int grid = blockIdx.z, i0 = blockIdx.x * 64, j0 = blockIdx.y * 4;
@@ -772,7 +784,7 @@ __global__ __launch_bounds__(256, (STAGE == 2 ? 5 : 4) - (WIDE ? 1 : 0)) void k_
                                                   double* __restrict__ Out, double* __restrict__ Aout, Geo g,
                                                   Consts k, Scal* __restrict__ sc, double* __restrict__ part,
                                                   int nparts) {
-  if (sc->stop) return;  // grid-uniform
+  if (sc->stop) return;  // per wave: no barrier follows
   // part (stage 2 of a CFL step after the first): fold the new state's wave
   // speeds into the time-step partials; every lane reaches the fold
   double s = 0.0, r = 1e300;
@@ -866,7 +878,7 @@ __global__ __launch_bounds__(256) void k_update_comps2d(const double* __restrict
                                                         const double* __restrict__ Nb, const double* __restrict__ Ain,
                                                         double* __restrict__ Out, double* __restrict__ Aout, Geo g, Consts k,
                                                         Scal* __restrict__ sc, double* __restrict__ part, int nparts) {
-  if (sc->stop) return;  // grid-uniform
+  if (block_stopped(sc)) return;
   double cfl_s = 0.0, cfl_r = 1e300;
   const bool fold = STAGE == 2 && part != nullptr;
   update_comps_row<STAGE, WIDE>(S, E, Nb, Ain, Out, Aout, g, k, sc->dt, blockIdx.x, blockIdx.y, blockIdx.z, sc, 0, fold,
@@ -1089,7 +1101,7 @@ __global__ __launch_bounds__(256, STAGE == 2 ? 3 : 2) void k_fused2d(const doubl
                                                     Scal* __restrict__ sc, double* __restrict__ part, int nparts,
                                                     int nstrips, int nchunks, int rows) {
   const Geo& g0 = g_in;
-  if (sc->stop) return;  // grid-uniform
+  if (block_stopped(sc)) return;
   int t;
   if (!xcd_tile(blockIdx.x, gridDim.x, nstrips * nchunks, t)) return;  // block-uniform
   using LD = FusedLds<STAGE>;
@@ -2175,7 +2187,7 @@ __global__ __launch_bounds__(256) void k_bphase_nodes(BArgs a, Consts k) {
 // Four blocks per item, one for each of its rows.
 template <int STAGE, bool WIDE>
 __global__ __launch_bounds__(256) void k_bphase_update(BArgs a, Consts k) {
-  if (a.sc->stop) return;
+  if (block_stopped(a.sc)) return;
   const BItem& w = a.items[a.n_cfl + a.n_halo + a.n_edge + a.n_node + (blockIdx.x >> 2)];
   const BMember& M = a.mem[w.m];
   const double dt = member_dt(a, w.m, k);
