@@ -524,18 +524,21 @@ __device__ __forceinline__ int wall_mask(const Geo& g, int grid, int i, int j) {
 }
 
 // The new conservative values of a node (the squares of the momenta summed in
-// component order), and W, x and y derivative of the component done last.
+// component order).
 struct NewNode {
-  double rho = 0.0, mom2 = 0.0, ener = 0.0, mU = 0.0, mV = 0.0, W, GX, GY;
+  double rho = 0.0, mom2 = 0.0, ener = 0.0, mU = 0.0, mV = 0.0;
 };
 
 // Components c0 .. c1 - 1 of node (i, j): the new values and derivatives, stored
-// in Out; stage 1 also stores the accumulators.
-template <int STAGE, class NF, bool WIDE>
+// in Out and handed to done(c, W, x derivative, y derivative); stage 1 also
+// stores the accumulators.  (Left in a struct instead, the last component's
+// results cost k_update2d<1, false> eight spilled registers: 1.315 against
+// 1.266 ms at 2048^2.)
+template <int STAGE, class NF, bool WIDE, class Done>
 __device__ __forceinline__ void update_comps(const double* __restrict__ S, const double* __restrict__ E, const NF& nf,
                                              const double* __restrict__ Ain, double* __restrict__ Out,
                                              double* __restrict__ Aout, const Geo& g, const Consts& k, double dt, int i,
-                                             int j, int grid, int c0, int c1, NewNode& v) {
+                                             int j, int grid, int c0, int c1, const Done& done) {
   const long pl = g.plane, o = at(g, j, i);
   const int r = grid;
   const long so = o + (grid ? g.dshift : 0);  // the dual planes are shifted along bounded axes
@@ -610,16 +613,7 @@ __device__ __forceinline__ void update_comps(const double* __restrict__ S, const
     __builtin_nontemporal_store((double)(W), &out[c * pl]);
     __builtin_nontemporal_store((double)(GX), &out[(4 + c) * pl]);
     __builtin_nontemporal_store((double)(GY), &out[(8 + c) * pl]);
-    if (c == 0) v.rho = W;
-    else if (c == 3) v.ener = W;
-    else {
-      v.mom2 = v.mom2 + W * W;
-      if (c == 1) v.mU = W;
-      else v.mV = W;
-    }
-    v.W = W;
-    v.GX = GX;
-    v.GY = GY;
+    done(c, W, GX, GY);
   }
 }
 
@@ -656,7 +650,16 @@ __device__ __forceinline__ void update_node(const double* __restrict__ S, const 
                                             int i, int j, int grid, Scal* sc, int member, bool want_cfl,
                                             double& cfl_s, double& cfl_r) {
   NewNode v;
-  update_comps<STAGE, NF, WIDE>(S, E, nf, Ain, Out, Aout, g, k, dt, i, j, grid, 0, 4, v);
+  update_comps<STAGE, NF, WIDE>(S, E, nf, Ain, Out, Aout, g, k, dt, i, j, grid, 0, 4,
+                                [&](int c, double W, double, double) {
+                                  if (c == 0) v.rho = W;
+                                  else if (c == 3) v.ener = W;
+                                  else {
+                                    v.mom2 = v.mom2 + W * W;
+                                    if (c == 1) v.mU = W;
+                                    else v.mV = W;
+                                  }
+                                });
   update_check<STAGE>(v, k, i, j, grid, sc, member, want_cfl, cfl_s, cfl_r);
 }
 
@@ -840,16 +843,17 @@ __device__ __forceinline__ void update_comps_row(const double* __restrict__ S, c
   const bool mine = i < g.nx && j < g.ny;
   if (mine) {
     const NodeFluxGlobal nf{Nb + (long)grid * 16 * g.plane + at(g, j, i), g.plane, g.pitch};
-    NewNode v;
-    update_comps<STAGE, NodeFluxGlobal, WIDE>(S, E, nf, Ain, Out, Aout, g, k, dt, i, j, grid, c, c + 1, v);
-    sW[c][tx] = v.W;
+    double W, GX, GY;
+    update_comps<STAGE, NodeFluxGlobal, WIDE>(S, E, nf, Ain, Out, Aout, g, k, dt, i, j, grid, c, c + 1,
+                                              [&](int, double w, double gx, double gy) { W = w, GX = gx, GY = gy; });
+    sW[c][tx] = W;
     // ghosts, in stored node coordinates
     const int si = i + (grid ? g.sx : 0), sj = j + (grid ? g.sy : 0);
     const int mx = g.nx + (grid ? g.sx : 0), my = g.ny + (grid ? g.sy : 0);
     if (si <= HALO || sj <= HALO || si >= mx - 1 - HALO || sj >= my - 1 - HALO) {
 #pragma unroll 1
       for (int f = 0; f < 3; ++f) {
-        const double val = f == 0 ? v.W : (f == 1 ? v.GX : v.GY);
+        const double val = f == 0 ? W : (f == 1 ? GX : GY);
         double* P = Out + (long)(grid * 12 + f * 4 + c) * g.plane;
         auto put = [&](int gj, double vy, bool real) {  // row gj holds vy at column si
           if (!real) P[at(g, gj, si)] = vy;
