@@ -288,10 +288,10 @@ fdcgks_status fdcgks_debug_intermediates(fdcgks_problem* pb, double dt, double* 
  * interface buffer).  0 runs the separate interface sweep and update
  * through the interface buffer (the interface and update launch shapes then
  * apply).  2 chooses the fused kernel where its row chunks are tall, i.e.
- * ny * ceil(nx / 61) >= 40 * (compute units): about 780^2 and up on MI355X.
- * Bitwise the same results.  Periodic problems with flux_order 6 (the others
- * always take the separate sweeps); it takes precedence over
- * FDCGKS_OPT_FUSE_NODES.
+ * ny * ceil(nx / 61) >= 40 * (compute units): about 780^2 and up on MI355X
+ * (FP32 fluxes: 128 instead of 40, about 1410^2 and up); results are bitwise
+ * the same.  Periodic problems with flux_order 6 (the others always take the
+ * unfused sweeps); it takes precedence over FDCGKS_OPT_FUSE_NODES.
  * FDCGKS_OPT_FUSED_ROWS (default 0): node rows per block of that kernel;
  * 0 chooses about two blocks per compute unit (three at stage 2).
  * EINVAL for an unknown option or an invalid value. */

@@ -2526,10 +2526,16 @@ enum { STAGE_SEPARATE = 0, STAGE_FUSE_NODES = 1, STAGE_FUSE_IFACE = 2, STAGE_JOI
 // Per step, fused against unfused, by strips x rows per compute unit: 18
 // (512^2) 436 against 324 us, 33 (700^2) 567 against 587, 36 598 against 603,
 // 63 (1400x700) 932 against 1097, 68 (1024^2) 977 against 1156, 126 (1400^2)
-// 1785 against 2265.
+// 1785 against 2265; characteristic variables 44 (800^2) 777 against 795, 68
+// 1090 against 1245, 126 1980 against 2389.  FP32 fluxes: the sweeps take less
+// and the lock step costs as much, so it needs 64 rows a chunk: 44 882 against
+// 753 us, 68 1254 against 1178, 126 2304 against 2284, 272 (2048^2) 4761
+// against 4782 (characteristic variables 914 against 787, 1336 against 1231,
+// 2510 against 2382, 4996 against 5026).
 bool fused_pays(const fdcgks_problem* pb) {
   const long strips = ceil_div(pb->g.nx, FS_W);
-  return (long)pb->g.ny * strips >= 40L * pb->ncu;
+  const long per_cu = pb->prm.flux_precision == FDCGKS_FP32_FLUX ? 128 : 40;
+  return (long)pb->g.ny * strips >= per_cu * pb->ncu;
 }
 // Unfused stages join their launches at every size (k_sweeps2d has both sides
 // measured) unless the caller chose launch shapes, which the launches of their
