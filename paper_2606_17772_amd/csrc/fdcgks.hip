@@ -2291,6 +2291,7 @@ struct fdcgks_problem {
   Consts k;
   Geo g;
   hipStream_t stream = nullptr;
+  int dev = 0;          // the device that holds the planes (current when the problem was made)
   int ngrid = 0;        // grids present (2D: 2; 1D: 1 or 2)
   int nplanes = 0;      // state planes per buffer
   double* S[2] = {nullptr, nullptr};  // ping-pong state
@@ -2366,13 +2367,29 @@ void free_all(fdcgks_problem* pb) {
 
 int ceil_div(long a, long b) { return (int)((a + b - 1) / b); }
 
-// Whether a kernel of the current device may access `count` doubles at p:
-// memory of this device, managed or pinned, all inside one allocation.
-// Anything else handed over as a device pointer keeps to the runtime's copies.
-bool kernel_reaches(const void* p, size_t count) {
+// Makes device `dev` current while it lives.
+struct OnDevice {
+  int prev = -1;
+  hipError_t err;
+  explicit OnDevice(int dev) {
+    int cur = dev;
+    err = hipGetDevice(&cur);
+    if (err != hipSuccess || cur == dev) return;
+    err = hipSetDevice(dev);
+    if (err == hipSuccess) prev = cur;
+  }
+  ~OnDevice() {
+    if (prev >= 0) (void)hipSetDevice(prev);
+  }
+  OnDevice(const OnDevice&) = delete;
+};
+// Whether a kernel of device `dev` may access `count` doubles at p: memory
+// allocated on that device, all inside one allocation.  Anything else handed
+// over as a device pointer (another device's, managed or pinned memory) keeps
+// to the runtime's copies.
+bool kernel_reaches(int dev, const void* p, size_t count) {
   hipPointerAttribute_t at;
-  int dev = -1;
-  if (hipPointerGetAttributes(&at, p) != hipSuccess || hipGetDevice(&dev) != hipSuccess) {
+  if (hipPointerGetAttributes(&at, p) != hipSuccess) {
     (void)hipGetLastError();
     return false;
   }
@@ -2946,9 +2963,9 @@ fdcgks_status fdcgks_create(const fdcgks_params* p, void* hip_stream, fdcgks_pro
   pb->ngrid = p->dim == 2 ? 2 : (p->dual_1d ? 2 : 1);
   pb->nplanes = (int)state_planes(*p);
   {
-    int dev = 0, cu = 0;
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cu > 0)
+    int cu = 0;
+    if (hipGetDevice(&pb->dev) == hipSuccess &&
+        hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, pb->dev) == hipSuccess && cu > 0)
       pb->ncu = cu;
   }
   size_t sbytes = (size_t)pb->nplanes * g.plane * sizeof(double);
@@ -2997,6 +3014,8 @@ static fdcgks_status copy_grid(fdcgks_problem* pb, int grid, double* const* ptrs
   const int mx = grid_nx(pb, grid), my = grid_ny(pb, grid);
   if (row_stride == 0) row_stride = mx;
   if (row_stride < mx) return fail(pb, FDCGKS_EINVAL, "row_stride %ld below the row length %d", (long)row_stride, mx);
+  const OnDevice on(pb->dev);  // a launch takes the current device, a copy did not
+  HIPCHK(pb, on.err);
   double* base = pb->S[pb->cur] + (long)grid * (pb->prm.dim == 2 ? 12 : 6) * g.plane;
   size_t row = (size_t)mx * sizeof(double), upitch = (size_t)row_stride * sizeof(double);
   if (!on_device && row_stride == mx) {
@@ -3022,7 +3041,7 @@ static fdcgks_status copy_grid(fdcgks_problem* pb, int grid, double* const* ptrs
   if (on_device) {
     const size_t need = (size_t)row_stride * my * (ncomp - 1) + (size_t)row_stride * (my - 1) + mx;
     bool ok = true;
-    for (int f = 0; f < nfield; ++f) ok = ok && kernel_reaches(ptrs[f], need);
+    for (int f = 0; f < nfield; ++f) ok = ok && kernel_reaches(pb->dev, ptrs[f], need);
     if (ok) {
       launch_state_io(pb->stream, g, base, ptrs, nfield, ncomp, mx, my, row_stride, to_device_state);
       return launch_check(pb, "state copy");
@@ -3409,7 +3428,7 @@ fdcgks_status fdcgks_step_vjp(fdcgks_problem* pb, double dt, const double* lam_o
   // both grids' planes between the padded layout and a dense array, one launch
   // a grid; an array the kernels cannot reach goes plane by plane
   auto planes = [&](double* padded, double* dense, bool in) -> fdcgks_status {
-    const bool direct = kernel_reaches(dense, (size_t)total);
+    const bool direct = kernel_reaches(pb->dev, dense, (size_t)total);
     for (int gr = 0; gr < 2; ++gr) {
       const size_t n = (size_t)mx[gr] * my[gr], row = (size_t)mx[gr] * sizeof(double);
       double* d = dense + (gr ? 12 * (size_t)mx[0] * my[0] : 0);
@@ -3597,6 +3616,7 @@ struct fdcgks_batch {
   fdcgks_params prm0;
   Consts k;
   hipStream_t stream = nullptr;
+  int dev = 0;  // the device that holds the members' planes
   std::vector<BMember> mem;
   BMember* mem_d = nullptr;
   std::vector<void*> allocs;
@@ -3730,6 +3750,7 @@ fdcgks_status fdcgks_batch_create(int32_t count, const fdcgks_params* params, vo
   b->count = count;
   b->prm0 = params[0];
   b->stream = (hipStream_t)hip_stream;
+  b->dev = dev;
   // scheme constants (shared)
   const fdcgks_params& p = params[0];
   Consts& k = b->k;
@@ -3843,6 +3864,8 @@ fdcgks_status fdcgks_batch_create(int32_t count, const fdcgks_params* params, vo
 
 static fdcgks_status batch_copy(fdcgks_batch* b, int m, int grid, double* const* ptrs, int to_dev, int on_device) {
   const Geo& g = b->mem[m].g;
+  const OnDevice on(b->dev);  // as copy_grid
+  BHIPCHK(b, on.err);
   double* base = b->mem[m].S[b->cur] + (long)grid * 12 * g.plane;
   const int mx = g.nx + (grid ? g.sx : 0), my = g.ny + (grid ? g.sy : 0);  // stored nodes of the grid
   size_t row = (size_t)mx * sizeof(double);
@@ -3853,7 +3876,7 @@ static fdcgks_status batch_copy(fdcgks_batch* b, int m, int grid, double* const*
   bool direct = true;
   for (int f = 0; f < 3; ++f) {
     stage[f] = on_device ? ptrs[f] : b->mem[m].E + f * 4 * dense;
-    direct = direct && (!on_device || kernel_reaches(stage[f], 4 * dense));
+    direct = direct && (!on_device || kernel_reaches(b->dev, stage[f], 4 * dense));
   }
   if (to_dev && !on_device)
     for (int f = 0; f < 3; ++f)
