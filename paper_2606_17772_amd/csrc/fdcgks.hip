@@ -2400,8 +2400,8 @@ bool kernel_reaches(int dev, const void* p, size_t count) {
     (void)hipGetLastError();
     return false;
   }
-  const char* end = static_cast<const char*>(p) + count * sizeof(double);
-  return (reinterpret_cast<uintptr_t>(p) & 7) == 0 && end <= static_cast<const char*>(lo) + len;
+  const size_t before = static_cast<const char*>(p) - static_cast<const char*>(lo);
+  return (reinterpret_cast<uintptr_t>(p) & 7) == 0 && before <= len && count <= (len - before) / sizeof(double);
 }
 // One grid's planes in or out (k_state_io); base: the grid's first plane.
 void launch_state_io(hipStream_t stream, const Geo& g, double* base, double* const* ptrs, int nfield, int ncomp, int mx,
@@ -3038,8 +3038,9 @@ static fdcgks_status copy_grid(fdcgks_problem* pb, int grid, double* const* ptrs
     HIPCHK(pb, hipStreamSynchronize(pb->stream));
     return FDCGKS_OK;
   }
-  if (on_device) {
-    const size_t need = (size_t)row_stride * my * (ncomp - 1) + (size_t)row_stride * (my - 1) + mx;
+  size_t need = 0;  // doubles from a field's first to its last; a stride for which that has no number is left to the copies
+  if (on_device && !__builtin_mul_overflow((size_t)row_stride, (size_t)my * ncomp - 1, &need) &&
+      !__builtin_add_overflow(need, (size_t)mx, &need)) {
     bool ok = true;
     for (int f = 0; f < nfield; ++f) ok = ok && kernel_reaches(pb->dev, ptrs[f], need);
     if (ok) {

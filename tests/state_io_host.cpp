@@ -144,5 +144,9 @@ int main(int, char** argv) {
       call("batch_set_" + t, dev, [&] { return fdcgks_batch_set_state(b, 0, 0, a[0], a[1], a[2], on); });
       call("batch_get_" + t, dev, [&] { return fdcgks_batch_get_state(b, 0, 1, a[0], a[1], a[2], on); });
     }
+  double* m = static_cast<double*>(mine);
+  for (int e : {59, 60, 61, 62})
+    call("get_stride" + std::to_string(e), 0,
+         [&] { return fdcgks_get_state(pb, 0, m, m + field, m + 2 * field, (int64_t)1 << e, 1); });
   return 0;
 }

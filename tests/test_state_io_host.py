@@ -11,6 +11,7 @@ import pytest
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB = os.path.join(os.path.dirname(HERE), "paper_2606_17772_amd", "libfdcgks.so")
 HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+EHIP = -3
 
 
 @pytest.fixture(scope="module")
@@ -38,3 +39,13 @@ def test_kernels_run_on_the_problems_device(calls, call, current):
         c = calls[f"{call}_{where}{tail}"]
         assert c["status"] == 0 and c["current"] == current
         assert c["launches"] == [] and c["copies"] == 12, c
+
+
+@pytest.mark.parametrize("e", [59, 60, 61, 62])
+def test_row_strides_beyond_the_address_space(calls, e):
+    """2^e doubles a row: their bytes, or the arrays', do not fit 64 bits.  No
+    kernel runs; the copies refuse a pitch below the row length."""
+    c = calls[f"get_stride{e}"]
+    assert c["launches"] == []
+    if e >= 61:
+        assert c["status"] == EHIP and c["copies"] == 0
