@@ -272,7 +272,8 @@ fdcgks_status fdcgks_debug_intermediates(fdcgks_problem* pb, double dt, double* 
  * The shape changes only the launch, never the arithmetic: results are
  * bitwise identical for every valid shape.  Unfused stages run their two
  * sweeps in one launch of fixed shape and update by component; setting any of
- * the three selects a launch per kernel, with the shapes set.
+ * the three selects a launch per kernel, with the shapes set, until
+ * fdcgks_autotune decides between the two.
  * FDCGKS_OPT_FUSE_NODES (default 0): 1 makes 2D steps evaluate the nodal fluxes
  * inside the update kernel (per 64 x 4 tile plus a one-node halo, in LDS)
  * instead of a separate node sweep through a node buffer; the node and
@@ -309,8 +310,10 @@ fdcgks_status fdcgks_get_option(const fdcgks_problem* pb, int32_t option, int64_
 
 /* Autotuner: times every valid candidate block shape of the three stage-1
  * kernels (reps launches each, HIP events on the problem's stream) on the
- * current state at its CFL 0.4 time step and keeps the fastest per kernel
- * (they apply where a launch per kernel runs, see FDCGKS_OPT_TILE_EDGE).
+ * current state at its CFL 0.4 time step and keeps the fastest per kernel;
+ * then an unfused stage 1 as a launch per kernel with those shapes against the
+ * joined launches, and keeps the faster for unfused stages from then on
+ * (whatever shapes were set before).
  * The state is not advanced (the stage scratch buffers are overwritten).
  * Synchronises the stream.  1D problems: nothing to tune, returns OK. */
 fdcgks_status fdcgks_autotune(fdcgks_problem* pb, int32_t reps);

@@ -399,7 +399,9 @@ class Problem:
         self._chk(self._L.fdcgks_set_option(self._h, self._TILES[kernel], int(x) | (int(y) << 16)))
 
     def autotune(self, reps=5):
-        """Time the candidate block shapes and keep the fastest; returns tiles()."""
+        """Time the candidate block shapes and keep the fastest, and keep the
+        faster of a launch per kernel in these shapes and the joined launches;
+        returns tiles()."""
         self._chk(self._L.fdcgks_autotune(self._h, reps))
         return self.tiles()
 

@@ -2314,7 +2314,7 @@ struct fdcgks_problem {
   // launch shapes of the interface, node and update kernels (x, y threads):
   // fdcgks_autotune's pick on the 2048^2 shear layer
   dim3 tile[3] = {dim3(64, 2), dim3(64, 1), dim3(128, 1)};
-  bool tile_set = false;  // the caller chose a shape: the launches that take shapes are used
+  bool tile_set = false;  // unfused stages as a launch per kernel, in these shapes (set_option, autotune), not joined
   // captured whole steps (one graph per ping-pong parity), replayed by fdcgks_step
   int graph_steps = 16;  // steps per captured graph; 0: separate launches
   bool fuse_nodes = false;  // node sweep inside the update kernel
@@ -2749,13 +2749,9 @@ bool tile_ok(int c, unsigned x, unsigned y) {
   return c != 0 || y % 2 == 0;
 }
 
-// Device milliseconds of `reps` launches of one stage-1 kernel with shape blk.
-float time_tile(fdcgks_problem* pb, int c, dim3 blk, int reps, hipEvent_t e0, hipEvent_t e1) {
-  auto one = [&]() {
-    if (c == 0) launch_edges<1>(pb, pb->S[pb->cur], blk);
-    else if (c == 1) launch_nodes<1>(pb, pb->S[pb->cur], blk);
-    else launch_update<1>(pb, pb->S[pb->cur], nullptr, pb->Sstar, pb->Acc, blk);
-  };
+// Device milliseconds of `reps` runs of one() on the problem's stream, or -1.
+template <class F>
+float time_reps(fdcgks_problem* pb, const F& one, int reps, hipEvent_t e0, hipEvent_t e1) {
   one();  // warm-up
   (void)hipEventRecord(e0, pb->stream);
   for (int r = 0; r < reps; ++r) one();
@@ -2764,6 +2760,23 @@ float time_tile(fdcgks_problem* pb, int c, dim3 blk, int reps, hipEvent_t e0, hi
   float ms = -1.f;
   if (hipEventElapsedTime(&ms, e0, e1) != hipSuccess) return -1.f;
   return ms;
+}
+// ... of one stage-1 kernel with shape blk
+float time_tile(fdcgks_problem* pb, int c, dim3 blk, int reps, hipEvent_t e0, hipEvent_t e1) {
+  auto one = [&]() {
+    if (c == 0) launch_edges<1>(pb, pb->S[pb->cur], blk);
+    else if (c == 1) launch_nodes<1>(pb, pb->S[pb->cur], blk);
+    else launch_update<1>(pb, pb->S[pb->cur], nullptr, pb->Sstar, pb->Acc, blk);
+  };
+  return time_reps(pb, one, reps, e0, e1);
+}
+// ... of an unfused stage 1 as a step runs it: a launch per kernel fills the
+// ghosts first, the joined launches find them filled
+float time_stage(fdcgks_problem* pb, int mode, int reps, hipEvent_t e0, hipEvent_t e1) {
+  auto one = [&]() {
+    (void)stage2d<1>(pb, pb->S[pb->cur], nullptr, pb->Sstar, pb->Acc, mode, mode == STAGE_JOINED);
+  };
+  return time_reps(pb, one, reps, e0, e1);
 }
 
 // Boundary of 2D side k (x-low, x-high, y-low, y-high): its own entry, or bc.
@@ -3598,6 +3611,20 @@ fdcgks_status fdcgks_autotune(fdcgks_problem* pb, int32_t reps) {
       }
     }
     pb->tile[c] = pick;
+  }
+  // a launch per kernel with these shapes, or the joined launches (the better of two runs each)
+  if (!st) {
+    float sep = -1.f, joined = -1.f;
+    for (int r = 0; r < 2 && !st; ++r) {
+      const float a = time_stage(pb, STAGE_SEPARATE, reps, e0, e1), b = time_stage(pb, STAGE_JOINED, reps, e0, e1);
+      if (a < 0.f || b < 0.f) {
+        st = launch_check(pb, "autotune");
+        if (!st) st = fail(pb, FDCGKS_EHIP, "autotune timing failed");
+      }
+      sep = r == 0 ? a : std::min(sep, a);
+      joined = r == 0 ? b : std::min(joined, b);
+    }
+    if (!st) pb->tile_set = sep < joined;
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);

@@ -32,3 +32,32 @@ def test_fused_stage_by_precision(n, fp32, route, recon):
     """FP32 fluxes want row chunks three times as tall (800^2: 0.88 fused
     against 0.75 ms unfused; FP64 0.70 against 0.75)."""
     assert _route(_uniform(n, n, fp32_flux=fp32, recon_vars=recon)) == route
+
+
+def test_autotune_decides_the_launches():
+    """A chosen shape selects a launch per kernel; autotune times that against
+    the joined launches and keeps the faster, whatever was chosen before (at
+    96 x 48 the joined ones: 41 against 73 us a step).  The shapes it reports
+    give the same results when set."""
+    import workloads as WL
+    pr = WL.random_smooth2d(96, 48, seed=3)
+
+    def make():
+        pb = _uniform(96, 48)
+        for g, S in ((0, pr.P), (1, pr.D)):
+            pb.set_state_stacked(g, S)
+        return pb
+
+    a, b, c = make(), make(), make()
+    assert _route(a) == "joined"
+    for g, S in ((0, pr.P), (1, pr.D)):
+        a.set_state_stacked(g, S)
+    a.set_tile("update", 32, 4)
+    tiles = a.autotune(reps=5)
+    for kernel, (x, y) in tiles.items():
+        b.set_tile(kernel, x, y)
+    assert a.tiles() == b.tiles() == tiles
+    for pb in (a, b, c):
+        assert pb.step(nsteps=3, cfl=0.4)[1] == 3
+    assert np.array_equal(a.get_state_all(), c.get_state_all()) and np.array_equal(b.get_state_all(), c.get_state_all())
+    assert _route(b) == "separate" and _route(a) == "joined"
