@@ -61,3 +61,51 @@ def test_autotune_decides_the_launches():
         assert pb.step(nsteps=3, cfl=0.4)[1] == 3
     assert np.array_equal(a.get_state_all(), c.get_state_all()) and np.array_equal(b.get_state_all(), c.get_state_all())
     assert _route(b) == "separate" and _route(a) == "joined"
+
+
+def _pinned(shape):
+    import torch
+    return torch.zeros(shape, dtype=torch.float64, pin_memory=True)
+
+
+def test_pinned_arrays_as_device_pointers():
+    """Memory that a kernel of the library does not take directly, handed over
+    as a device pointer, goes through the runtime's copies: states of a problem
+    and a batch in and out, and the adjoint's arrays, equal to the kernel route
+    bit for bit."""
+    import ctypes as C
+
+    import torch
+
+    import workloads as WL
+    from paper_2606_17772_amd import Batch, Problem, _lib
+    L = _lib.load()
+    nx, ny = 37, 21
+    pr = WL.random_smooth2d(nx, ny, seed=8)
+    prm = gpu_params(settings(dim=2, nx=nx, ny=ny, lx=1.0))
+    pb, b = Problem(prm), Batch([prm])
+
+    def ptrs(t):
+        return [C.c_void_p(t.data_ptr() + 8 * 4 * q * ny * nx) for q in range(3)]
+
+    src, dst = _pinned((12, ny, nx)), _pinned((12, ny, nx))
+    for g, S in ((0, pr.P), (1, pr.D)):
+        src.copy_(torch.from_numpy(S))
+        assert L.fdcgks_set_state(pb._h, g, *ptrs(src), 0, 1) == 0
+        assert L.fdcgks_batch_set_state(b._h, 0, g, *ptrs(src), 1) == 0
+        torch.cuda.synchronize()
+        assert np.array_equal(pb.get_state_stacked(g), S) and np.array_equal(b.get_state_stacked(0, g), S)
+        for call in (lambda: L.fdcgks_get_state(pb._h, g, *ptrs(dst), 0, 1),
+                     lambda: L.fdcgks_batch_get_state(b._h, 0, g, *ptrs(dst), 1)):
+            dst.zero_()
+            assert call() == 0
+            torch.cuda.synchronize()
+            assert np.array_equal(dst.numpy(), S)
+    lam = torch.from_numpy(np.random.default_rng(2).standard_normal((2, 12, ny, nx)))
+    lin, lout = _pinned(lam.shape), _pinned(lam.shape)
+    lin.copy_(lam)
+    assert L.fdcgks_step_vjp(pb._h, C.c_double(1e-3), C.c_void_p(lin.data_ptr()), C.c_void_p(lout.data_ptr()), 1) == 0
+    torch.cuda.synchronize()
+    want = pb.step_vjp(1e-3, lam.numpy())
+    # the reverse sweeps add by atomics: repeated calls differ by round-off (see test_gpu_adjoint's device arrays)
+    assert np.abs(lout.numpy() - want).max() <= 1e-12 * np.abs(want).max()
