@@ -38,8 +38,7 @@ HBM_BYTES_PER_NODE_STAGE = 288  # algorithmic: stage 1 reads 12 / writes 24 doub
 # bytes per launch are from the rocprofv3 counters of this kernel
 # (profiles/k_fused2d_shear2048.md: 64 x (ADD + MUL + 2 FMA + TRANS) wave
 # instructions; FETCH_SIZE x 2.000 + WRITE_SIZE x 1.000 after the copy-kernel
-# calibration).  Both are None whenever the kernel has changed since the
-# counters were taken.
+# calibration).
 FLOPS_PER_NODE_FUSED_STAGE1 = 4415
 TRAFFIC_BYTES_PER_LAUNCH_FUSED_STAGE1 = 5.068e9
 # With --separate: the stage-1 interface sweep k_edges2d<1,double,false>, unit
@@ -51,14 +50,18 @@ TRAFFIC_BYTES_PER_LAUNCH_FUSED_STAGE1 = 5.068e9
 FLOPS_PER_IFACE_POINT_STAGE1 = 5618
 FLOPS_EXECUTED_PER_IFACE_POINT_STAGE1 = 3789
 TRAFFIC_BYTES_PER_LAUNCH_STAGE1 = 4.473e9
+# The node sweep, unit one node, 2 (n+2)^2 per launch (same profile): with the
+# interface points it makes up the joined sweeps' launch (k_sweeps2d).
+FLOPS_PER_NODE_SWEEP_STAGE1 = 499
 # 3D leg: the stage-1 interface sweep k_edges3d<true,false>, unit one solve
 # (12 per cell), from profiles/k_edges3d_taylor_green128.md (same counters).
 FLOPS_PER_SOLVE_3D_STAGE1 = 2843
 
 
 # Launch shapes fdcgks_autotune picks on this workload (interface sweep,
-# node sweep, update); fixed here so that profiled runs launch exactly what
-# the timed run launches.
+# node sweep, update), for --separate: setting a shape selects a launch per
+# kernel.  Without --separate or --tiles no shape is set, and unfused problems
+# take the library's own choice, the joined launches.
 DEFAULT_TILES = "edge=64x2,node=64x1,update=128x1"
 
 
@@ -75,8 +78,8 @@ def parse():
     ap.add_argument("--no-batch", action="store_true", help="skip the batched-vs-per-problem comparison")
     ap.add_argument("--batch-steps", type=int, default=32)
     ap.add_argument("--no-adjoint", action="store_true", help="skip the adjoint-vs-forward comparison")
-    ap.add_argument("--tiles", default=DEFAULT_TILES,
-                    help="launch shapes kernel=XxY,... (default: the autotuner's pick at 2048^2)")
+    ap.add_argument("--tiles", default="",
+                    help="launch shapes kernel=XxY,... (default: none set; with --separate the autotuner's pick at 2048^2)")
     ap.add_argument("--autotune", action="store_true", help="run fdcgks_autotune instead of --tiles")
     ap.add_argument("--separate", action="store_true",
                     help="run the separate interface sweep, node sweep and update (no fused stage kernel)")
@@ -92,6 +95,35 @@ def parse():
     ap.add_argument("--copy-calibration", action="store_true",
                     help="run one plain 512 MiB device copy first (reference for HBM byte counters)")
     return ap.parse_args()
+
+
+def parse_tiles(text):
+    """{"edge": (64, 2), ...} of "edge=64x2,..."."""
+    items = (item.split("=") for item in text.split(",") if item)
+    return {name: tuple(int(v) for v in xy.split("x")) for name, xy in items}
+
+
+def stage_roofline(kms, kn, n):
+    """(stage, roofline entry) of the default workload's dominant stage-1 launch
+    from the per-kernel milliseconds of `kn` steps: the fused stage has no
+    interface slot, and the joined sweeps, both in the interface slot, no node
+    slot."""
+    if kms["edge1"] == 0.0:
+        stage, kernel = "fused", "k_fused2d<1,double,false> (stage-1 interface sweep fused with the update)"
+        slot, flops, traffic = "update1", FLOPS_PER_NODE_FUSED_STAGE1 * 2 * n * n, TRAFFIC_BYTES_PER_LAUNCH_FUSED_STAGE1
+    else:
+        slot, flops, traffic = "edge1", FLOPS_EXECUTED_PER_IFACE_POINT_STAGE1 * 2 * (n + 3) ** 2, None
+        if kms["node1"] == 0.0:
+            stage, kernel = "joined", "k_sweeps2d<1,double,false> (stage-1 interface and node sweeps in one launch)"
+            flops += FLOPS_PER_NODE_SWEEP_STAGE1 * 2 * (n + 2) ** 2
+        else:
+            stage, kernel = "separate", "k_edges2d<1,double,false> (stage-1 interface sweep)"
+            traffic = TRAFFIC_BYTES_PER_LAUNCH_STAGE1
+    launch_ms = kms[slot] / kn
+    achieved = flops / (launch_ms * 1e-3) / 1e12
+    return stage, {"bound": "alu", "achieved": round(achieved, 3), "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s",
+                   "frac": round(achieved / PEAK_FP64_TFLOPS, 4), "traffic": traffic, "kernel": kernel,
+                   "avg_launch_ms": round(launch_ms, 4)}
 
 
 def _host_info():
@@ -706,14 +738,13 @@ def main():
         T = torch.from_numpy(S).to(dev)
         pb.set_state(g, T[0:4].contiguous(), T[4:8].contiguous(), T[8:12].contiguous())
     torch.cuda.synchronize()
+    chosen = parse_tiles(args.tiles or (DEFAULT_TILES if args.separate else ""))
     if args.autotune:
-        tiles = pb.autotune(reps=5)
-    else:
-        for item in args.tiles.split(","):
-            name, xy = item.split("=")
-            x, y = (int(v) for v in xy.split("x"))
-            pb.set_tile(name, x, y)
-        tiles = pb.tiles()
+        picks = pb.autotune(reps=5)
+        chosen = picks if args.separate else {}  # else the launches autotune decided on stay
+    for name, (x, y) in chosen.items():
+        pb.set_tile(name, x, y)
+    shapes = pb.tiles()
     t = 0.0
     if args.warmup:
         t, _ = pb.step(nsteps=args.warmup, cfl=CFL, t=t)
@@ -732,26 +763,7 @@ def main():
     # per-kernel breakdown on the same stream (separate, untimed-for-value run)
     _, _, kms = pb.step_timed(nsteps=max(2, args.steps // 4), cfl=CFL, t=t)
     kn = max(2, args.steps // 4)
-    fused = kms["edge1"] == 0.0  # no separate interface sweep ran
-    if fused:
-        # the fused kernel's launches are timed under the update slot
-        launch_ms = kms["update1"] / kn
-        flops_per_unit, units, traffic = FLOPS_PER_NODE_FUSED_STAGE1, 2 * n * n, TRAFFIC_BYTES_PER_LAUNCH_FUSED_STAGE1
-        kernel = "k_fused2d<1,double,false> (stage-1 interface sweep fused with the update)"
-    else:
-        launch_ms = kms["edge1"] / kn
-        flops_per_unit, units, traffic = FLOPS_EXECUTED_PER_IFACE_POINT_STAGE1, 2 * (n + 3) * (n + 3), \
-            TRAFFIC_BYTES_PER_LAUNCH_STAGE1
-        kernel = "k_edges2d<1,double,false> (stage-1 interface sweep)"
-    if flops_per_unit:
-        achieved = flops_per_unit * units / (launch_ms * 1e-3) / 1e12
-        roof = {"bound": "alu", "achieved": round(achieved, 3), "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s",
-                "frac": round(achieved / PEAK_FP64_TFLOPS, 4), "traffic": traffic}
-    else:
-        roof = {"bound": "alu", "achieved": None, "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s", "frac": None,
-                "traffic": None}
-    roof["kernel"] = kernel
-    roof["avg_launch_ms"] = round(launch_ms, 4)
+    stage, roof = stage_roofline(kms, kn, n)
     hbm_gbs = value * HBM_BYTES_PER_NODE_STAGE / 1e9
     out = {
         "metric": "node-updates/s per stage (FP64, 1 GPU)",
@@ -768,8 +780,8 @@ def main():
         "data": "synthetic",
         "config": {"workload": f"2D Navier-Stokes double shear layer {n}x{n} primary + dual, Re=1e4, Pr=0.72, "
                                "CFL 0.5, (6-4) GENO, FP64", "nodes_per_stage": nodes, "stages_per_step": 2,
-                   "launch_shapes": {k2: f"{x}x{y}" for k2, (x, y) in tiles.items()}, "step_graphs": True,
-                   "stage": "fused" if fused else "separate"},
+                   "launch_shapes": {k2: f"{x}x{y}" for k2, (x, y) in shapes.items()}, "step_graphs": True,
+                   "stage": stage},
         "roofline": roof,
         "hbm_roofline": {"algorithmic_bytes_per_node_stage": HBM_BYTES_PER_NODE_STAGE,
                          "achieved_GBs": round(hbm_gbs, 1), "peak_GBs": PEAK_HBM_GBS,
@@ -785,21 +797,21 @@ def main():
         torch.cuda.empty_cache()
         pb = None
     if not args.no_fp32:
-        out["fp32_flux"] = fp32_flux_comparison(pr, n, tiles)
+        out["fp32_flux"] = fp32_flux_comparison(pr, n, chosen)
     if not args.no_char:
-        out["characteristic"] = characteristic_comparison(pr, n, tiles)
+        out["characteristic"] = characteristic_comparison(pr, n, chosen)
     if not args.no_order8:
-        out["order8"] = order8_comparison(pr, n, tiles)
+        out["order8"] = order8_comparison(pr, n, chosen)
     if not args.no_bounded:
         torch.cuda.empty_cache()
-        out["bounded"] = bounded_comparison(n, tiles)
+        out["bounded"] = bounded_comparison(n, chosen)
     if not args.no_graph:
         out["graph_replay"] = graph_comparison()
     if not args.no_3d:
         torch.cuda.empty_cache()
         out["three_d"] = three_d_leg(args.n3d)
     if not args.no_configs:
-        out["configs"] = config_legs(tiles)
+        out["configs"] = config_legs(chosen)
     if not args.no_batch:
         del pb
         torch.cuda.empty_cache()
