@@ -47,3 +47,27 @@ def test_tiles_are_chosen_only_when_asked_for(monkeypatch):
     monkeypatch.setattr(sys, "argv", ["bench.py"])
     assert bench.parse_tiles(bench.parse().tiles) == {}
     assert bench.parse_tiles(bench.DEFAULT_TILES) == {"edge": (64, 2), "node": (64, 1), "update": (128, 1)}
+
+
+def test_executed_count_against_the_source(tmp_path):
+    """The counted flop per interface point against the operations of the
+    source it is compiled from (the solver in primitive slopes; test_opcount.py
+    counts the form from moment vectors, which the FP32-flux variant runs).  The
+    compiler folds and shares some of them (a fifth at most), and writes out
+    exp (about 45 flop), erf (30), the reciprocal (10) and the square root (16)
+    that the source count takes as one each."""
+    import json
+    import shutil
+    import subprocess
+
+    import bench
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    if not os.path.exists(hipcc):
+        pytest.skip("hipcc not available")
+    exe = str(tmp_path / "opcount")
+    subprocess.run([hipcc, "-std=c++17", "-O1", "--cuda-host-only", "-x", "hip",
+                    os.path.join(ROOT, "tests", "opcount_slopes.cpp"), "-o", exe], check=True, capture_output=True)
+    c = json.loads(subprocess.run([exe], check=True, capture_output=True, text=True).stdout)
+    assert (c["erfc"], c["exp"], c["sqrt"], c["div"]) == (4, 6, 4, 18), c
+    written_out = 45 * c["exp"] + 30 * c["erfc"] + 10 * c["div"] + 16 * c["sqrt"]
+    assert 0.8 * c["arith"] < bench.FLOPS_EXECUTED_PER_IFACE_POINT_STAGE1 < c["arith"] + written_out, c
