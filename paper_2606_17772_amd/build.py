@@ -57,6 +57,19 @@ def build(verbose: bool = False, extra=()) -> str:
     return LIB
 
 
+def build_test_kernels() -> str:
+    """tests/libdevice_math.so: the library's elementary device routines behind
+    an entry that the GPU tests call (small: a few seconds)."""
+    src = os.path.join(ROOT, "tests", "device_math.hip")
+    out = os.path.join(ROOT, "tests", "libdevice_math.so")
+    r = subprocess.run([HIPCC, *FLAGS, src, "-o", out + ".tmp"], capture_output=True, text=True)
+    if r.returncode != 0:
+        sys.stderr.write(r.stdout + r.stderr)
+        raise RuntimeError("hipcc failed building libdevice_math.so")
+    os.replace(out + ".tmp", out)
+    return out
+
+
 if __name__ == "__main__":
     build(verbose="--verbose" in sys.argv,
           extra=["-Rpass-analysis=kernel-resource-usage"] if "--usage" in sys.argv else [])

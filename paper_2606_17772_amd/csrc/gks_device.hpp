@@ -47,7 +47,10 @@ template <class T> FDK_HD T sqr(T a) { return a * a; }
 
 // Reciprocal and square root of normal numbers: Newton steps on the hardware
 // estimates without the scaling and fix-up of the IEEE sequences (5 and 8
-// instructions instead of about 11 and 18; results within an ulp).  Not for
+// instructions instead of about 11 and 18).  The square root is the coupled
+// iteration for sqrt(x) and 1 / (2 sqrt(x)) with one correction by the
+// residual.  On the device both are right to 0.500 ulp at each of 400,000
+// points over 1e-290 .. 1e290, as the correctly rounded operations.  Not for
 // arguments that may be zero, denormal or infinite.
 template <class T> FDK_HD T m_recip(T x) { return T(1) / x; }
 FDK_HD double m_recip(double x) {
@@ -72,7 +75,7 @@ FDK_HD double m_sqrt_normal(double x) {
   return sqrt(x);
 #endif
 }
-// exp(-x) and 1 - exp(-x) for x >= 0, both to the last digits: -x = k ln 2 + r,
+// exp(-x) and 1 - exp(-x) for x >= 0, to 1.13 and 1.23 ulp: -x = k ln 2 + r,
 // expm1(r) = r + r^2 (1/2 + r q(r)) with q interpolated at Chebyshev nodes of
 // |r| <= ln(2) / 2 (relative error of exp below 8e-17 before rounding).
 FDK_HD void exp_neg(double x, double& E, double& one_minus_E) {
@@ -102,7 +105,8 @@ FDK_HD double g_tanh(double a) {
   exp_neg(2.0 * fabs(a), E, o);
   return copysign(o * m_recip(1.0 + E), a);
 }
-// erf(z) / 2 for |z| <= 1: z p(z^2), p interpolated at Chebyshev nodes of [0, 1] (relative error below 5e-17).
+// erf(z) / 2 for |z| <= 1, to 1.62 ulp: z p(z^2), p interpolated at Chebyshev nodes of [0, 1] (relative error
+// below 5e-17).
 FDK_HD double half_erf_small(double z) {
   const double t = z * z;
   double p = -0x1.ac9585a44fe29p-32;
@@ -696,7 +700,10 @@ template <class FT> FDK_HD void mom_full(const Prim<FT>& s, Mom<FT>& m) {
 FDK_HD void half_moms(double lam, double i2l, double U, double sgn, double& m0, double& x) {
   const double sl = m_sqrt_normal(lam), z = sl * U;
   // |z| <= 1 up to a normal Mach number of about 1.2; a wave goes through the
-  // library's erfc only if one of its points is beyond
+  // library's erfc only if one of its points is beyond.  1/2 - erf/2 is exact
+  // in the last digits of the whole, not of the smaller share; with erfc in its
+  // place the solver's error against extended precision is the same to 1% (40,000
+  // states each at normal Mach 0.3 to 2, densities up to 1e5 apart)
   if (fabs(z) <= 1.0) m0 = 0.5 + sgn * half_erf_small(z);
   else m0 = 0.5 * m_erfc(-sgn * z);
   double E, o;
