@@ -194,7 +194,10 @@ fdcgks_status fdcgks_step(fdcgks_problem* pb, double dt, double cfl, int32_t nst
  * receives the summed milliseconds between consecutive events for: halo fill,
  * interface sweep (stage 1), node sweep (1), assemble+update (1), interface
  * sweep (2), node sweep (2), assemble+update (2), step bookkeeping (CFL
- * reduction, dt, time advance).  Synchronous. */
+ * reduction, dt, time advance).  Where a launch does two of these, its time is
+ * in one slot and the other stays 0: the joined sweeps in the interface slot,
+ * the fused stage in the update slot, and the update that writes its ghosts
+ * leaves the halo slot to the call's first state.  Synchronous. */
 fdcgks_status fdcgks_step_timed(fdcgks_problem* pb, double dt, double cfl, int32_t nsteps, double t_end,
                                 double* t_inout, int32_t* steps_done, double* kernel_ms);
 
@@ -357,9 +360,10 @@ typedef struct fdcgks_batch fdcgks_batch; /* opaque, owned by the library */
 /* How a batched stage is launched.  PERSISTENT: one cooperative launch per
  * stage, sized to the co-resident grid, that walks the device work list in
  * three phases separated by grid barriers (CFL partials and halo; interface
- * and node sweeps; update).  PHASED: the same work list and device code as
- * one launch per phase (halo, interfaces, nodes, update), so that every
- * phase runs at its own occupancy.  GRAPH (default): the PHASED launches of
+ * and node sweeps; update); the slowest of the three on MI355X.  PHASED: the
+ * same work list as one launch per phase (CFL partials and the ghosts of a
+ * first state; interfaces; nodes; update, which writes its result's ghosts), so
+ * that every phase runs at its own occupancy.  GRAPH (default): the PHASED launches of
  * 16 steps captured as one HIP graph (per start parity and cfl, on first
  * use) and replayed; the last nsteps mod 16 steps launch separately.  All
  * give bitwise the same results. */

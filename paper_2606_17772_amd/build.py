@@ -26,17 +26,19 @@ FLAGS = [
     # the inlined stage code then does not depend on the kernel it sits in
     # (single problems, batches, fused and separate sweeps agree bit for bit)
     "-ffp-contract=on",
-    # instruction scheduling that groups memory clauses: the interface sweep
-    # then fits its registers without spilling (246 VGPRs), and a step is
-    # about 1% faster on the 2048^2 workload; the arithmetic is unchanged
+    # instruction scheduling that groups memory clauses.  The solver from moment
+    # vectors needed it to fit its registers (246 VGPRs, a 2048^2 step 1%
+    # faster); with the solver in primitive slopes it is within 1% of the
+    # compiler's own on every kernel (2048^2 step 3.72 ms either way).  The
+    # arithmetic does not depend on it
     "-mllvm", "-amdgpu-sched-strategy=max-memory-clause",
-    # no machine-level loop-invariant code motion: hoisted out of the phase
-    # loop of the solver adjoint (and of the persistent batch and 1D step
-    # loops), the 64-bit constants of erfc/exp and similar invariants are held
-    # in registers through every iteration and spill.  Measured on the 2048^2
-    # workload: step VJP -2.7%, persistent batch +27%, 1D runs +5-8%; the 2D
-    # interface, node and update sweeps compile to the same code, the other
-    # kernels within noise
+    # no machine-level loop-invariant code motion: hoisted out of the row loop of
+    # the fused stage (and of the 1D step and persistent batch loops), the 64-bit
+    # constants of exp and erf and similar invariants are held in registers
+    # through every iteration.  Without the flag a 2048^2 step takes 5.22 instead
+    # of 3.72 ms, a 1024^2 characteristic one 1.51 instead of 1.11, a step of 600
+    # nodes in 1D 35.9 instead of 29.1 us, the persistent batch 2.18 instead of
+    # 2.03 ms; the unfused sweeps and the adjoint are within 2%
     "-mllvm", "-disable-machine-licm",
     "-I", os.path.join(ROOT, "include"),
 ]

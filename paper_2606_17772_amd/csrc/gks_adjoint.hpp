@@ -84,15 +84,6 @@ FDK_HD int opaque_int(int x) {
   return x;
 }
 
-// A pointer the compiler cannot see through (address arithmetic on it stays
-// where it is written).
-template <class T> FDK_HD T* opaque_ptr(T* p) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("" : "+v"(p));
-#endif
-  return p;
-}
-
 // ------------------------------- reverse of the solvers in primitive slopes
 // The reverse follows the forward code's form (see gks_device.hpp): slopes of
 // (rho, U, V, theta), polynomials of the normal velocity, one set of 1D
