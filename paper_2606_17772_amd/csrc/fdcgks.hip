@@ -2551,8 +2551,9 @@ enum { STAGE_SEPARATE = 0, STAGE_FUSE_NODES = 1, STAGE_FUSE_IFACE = 2, STAGE_JOI
 // (512^2) 436 against 324 us, 33 (700^2) 567 against 587, 36 598 against 603,
 // 63 (1400x700) 932 against 1097, 68 (1024^2) 977 against 1156, 126 (1400^2)
 // 1785 against 2265; characteristic variables 44 (800^2) 777 against 795, 68
-// 1090 against 1245, 126 1980 against 2389.  FP32 fluxes: the sweeps take less
-// and the lock step costs as much, so it needs 64 rows a chunk: 44 882 against
+// 1090 against 1245, 126 1980 against 2389.  FP32 fluxes: unfused, the
+// sweeps run at three waves per SIMD (125 registers) where the fused kernel's
+// LDS holds stage 1 to two, so it needs 64 rows a chunk: 44 882 against
 // 753 us, 68 1254 against 1178, 126 2304 against 2284, 272 (2048^2) 4761
 // against 4782 (characteristic variables 914 against 787, 1336 against 1231,
 // 2510 against 2382, 4996 against 5026).
@@ -2780,9 +2781,9 @@ float time_tile(fdcgks_problem* pb, int c, dim3 blk, int reps, hipEvent_t e0, hi
 }
 // ... of an unfused stage 1 as a step runs it: a launch per kernel fills the
 // ghosts first, the joined launches find them filled
-float time_stage(fdcgks_problem* pb, int mode, int reps, hipEvent_t e0, hipEvent_t e1) {
+float time_stage(fdcgks_problem* pb, int mode, int reps, hipEvent_t e0, hipEvent_t e1, fdcgks_status& st) {
   auto one = [&]() {
-    (void)stage2d<1>(pb, pb->S[pb->cur], nullptr, pb->Sstar, pb->Acc, mode, mode == STAGE_JOINED);
+    if (!st) st = stage2d<1>(pb, pb->S[pb->cur], nullptr, pb->Sstar, pb->Acc, mode, mode == STAGE_JOINED);
   };
   return time_reps(pb, one, reps, e0, e1);
 }
@@ -3624,11 +3625,9 @@ fdcgks_status fdcgks_autotune(fdcgks_problem* pb, int32_t reps) {
   if (!st) {
     float sep = -1.f, joined = -1.f;
     for (int r = 0; r < 2 && !st; ++r) {
-      const float a = time_stage(pb, STAGE_SEPARATE, reps, e0, e1), b = time_stage(pb, STAGE_JOINED, reps, e0, e1);
-      if (a < 0.f || b < 0.f) {
-        st = launch_check(pb, "autotune");
-        if (!st) st = fail(pb, FDCGKS_EHIP, "autotune timing failed");
-      }
+      const float a = time_stage(pb, STAGE_SEPARATE, reps, e0, e1, st);
+      const float b = time_stage(pb, STAGE_JOINED, reps, e0, e1, st);
+      if (!st && (a < 0.f || b < 0.f)) st = fail(pb, FDCGKS_EHIP, "autotune timing failed");
       sep = r == 0 ? a : std::min(sep, a);
       joined = r == 0 ? b : std::min(joined, b);
     }
